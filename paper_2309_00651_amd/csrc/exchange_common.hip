@@ -1,10 +1,12 @@
 // Elementwise helpers of the exchange pipeline: float64 -> float32 staging
 // of the orbitals, zero fill (a kernel rather than a memset, so the calls stay
-// graph-capture friendly), the fixed-order float64 energy reduction, and the
-// optional input check (non-finite values, z band of the orbitals).
+// graph-capture friendly), the fixed-order float64 energy reduction, the
+// optional input check (non-finite values, z band of the orbitals), and the
+// resampling of reduced pair grids.
 #include <hip/hip_runtime.h>
 
 #include "hfx_internal.hpp"
+#include "resample.hpp"
 
 namespace hfx {
 

@@ -112,6 +112,27 @@ using P24x48 = FusedPipeline<float, 24, 16, 8, Sched<4, 12>, Sched<12, 4>, 144, 
 using P64x128 = FusedPipeline<float, 64, 16, 8, Sched<8, 16>, Sched<16, 8>, 256, Sched<8, 8>,
                               Sched<8, 8>, Sched<8, 8>, Sched<8, 8>, false, 256, 1024, false, false,
                               false, false, 128>;
+// Reduced pair grids of band-limited plans on grids that oversample the pair
+// densities twofold.
+// ReducedPipeline<T, forward points, inverse points, W, tile, plane threads,
+//                 x inv, y inv, z inv, pair_fwd threads, inv_acc threads,
+//                 psi J block in LDS, prefetch, flat loads [, z points]>
+using R64 = ReducedPipeline<float, 32, 48, 16, 8, 384, Sched<6, 8>, Sched<6, 8>, Sched<6, 8>, 256,
+                            384, true, true>;
+using R72 = ReducedPipeline<float, 36, 60, 16, 8, 480, Sched<6, 10>, Sched<6, 10>, Sched<6, 10>,
+                            256, 480, true, true>;
+using R80 = ReducedPipeline<float, 40, 60, 16, 8, 480, Sched<6, 10>, Sched<6, 10>, Sched<6, 10>,
+                            256, 480, true, true>;
+using R96 = ReducedPipeline<float, 48, 72, 16, 8, 576, Sched<9, 8>, Sched<9, 8>, Sched<9, 8>, 256,
+                            512, true, true>;
+using R108 = ReducedPipeline<float, 54, 80, 16, 8, 640, Sched<10, 8>, Sched<10, 8>, Sched<10, 8>,
+                             256, 512, true, true>;
+using R120 = ReducedPipeline<float, 60, 96, 16, 8, 768, Sched<12, 8>, Sched<12, 8>, Sched<8, 12>,
+                             256, 512, true, true>;
+using R128 = ReducedPipeline<float, 64, 96, 16, 8, 768, Sched<12, 8>, Sched<12, 8>, Sched<8, 12>,
+                             256, 512, true, true>;
+using R64x128 = ReducedPipeline<float, 32, 48, 16, 8, 384, Sched<6, 8>, Sched<6, 8>, Sched<8, 12>,
+                                256, 512, true, true, 0, 64, 96>;
 }  // namespace
 
 const Variant* variants_f32(int* count) {
@@ -148,6 +169,17 @@ const Variant* variants_f32(int* count) {
       P128h2::describe("f32-n128-h2"),
       P24x48::describe("f32-n24x48"),
       P64x128::describe("f32-n64x128"),
+  };
+  *count = (int)(sizeof(v) / sizeof(v[0]));
+  return v;
+}
+
+const Variant* reduced_f32(int* count) {
+  static const Variant v[] = {
+      R64::describe("f32-n64-r48"),       R72::describe("f32-n72-r60"),
+      R80::describe("f32-n80-r60"),       R96::describe("f32-n96-r72"),
+      R108::describe("f32-n108-r80"),     R120::describe("f32-n120-r96"),
+      R128::describe("f32-n128-r96"),     R64x128::describe("f32-n64x128-r48x96"),
   };
   *count = (int)(sizeof(v) / sizeof(v[0]));
   return v;

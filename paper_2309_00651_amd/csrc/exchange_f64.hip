@@ -62,6 +62,24 @@ using P120z = SplitPipeline<double, 120, 16, 240, 8, Sched<8, 15>, Sched<15, 8>,
                             Sched<8, 15>, Sched<15, 8>, Sched<8, 15>, Sched<15, 8>>;
 using P128z = SplitPipeline<double, 128, 16, 256, 8, Sched<8, 16>, Sched<16, 8>, 16, 256,
                             Sched<8, 16>, Sched<16, 8>, Sched<8, 16>, Sched<16, 8>>;
+// Reduced pair grids (see exchange_f32.hip).  Every plane of these fits in LDS,
+// also where the caller's grid takes the split plane pass.
+using R64 = ReducedPipeline<double, 32, 48, 16, 8, 384, Sched<6, 8>, Sched<6, 8>, Sched<6, 8>, 256,
+                            384, false, false>;
+using R72 = ReducedPipeline<double, 36, 60, 16, 8, 480, Sched<6, 10>, Sched<6, 10>, Sched<6, 10>,
+                            288, 480, false, false>;
+using R80 = ReducedPipeline<double, 40, 60, 16, 8, 480, Sched<6, 10>, Sched<6, 10>, Sched<6, 10>,
+                            320, 480, false, false>;
+using R96 = ReducedPipeline<double, 48, 72, 16, 8, 576, Sched<9, 8>, Sched<9, 8>, Sched<9, 8>, 384,
+                            576, false, false>;
+using R108 = ReducedPipeline<double, 54, 80, 16, 8, 640, Sched<10, 8>, Sched<10, 8>, Sched<10, 8>,
+                             432, 640, false, false>;
+using R120 = ReducedPipeline<double, 60, 96, 16, 8, 768, Sched<12, 8>, Sched<12, 8>, Sched<12, 8>,
+                             480, 768, false, false>;
+using R128 = ReducedPipeline<double, 64, 96, 16, 8, 768, Sched<12, 8>, Sched<12, 8>, Sched<12, 8>,
+                             512, 768, false, false>;
+using R64x128 = ReducedPipeline<double, 32, 48, 16, 8, 384, Sched<6, 8>, Sched<6, 8>, Sched<12, 8>,
+                                512, 768, false, false, 0, 64, 96>;
 }  // namespace
 
 const Variant* variants_f64(int* count) {
@@ -86,6 +104,17 @@ const Variant* variants_f64(int* count) {
       P128z::describe("f64-n128-z"),
       P24x48::describe("f64-n24x48"),
       P64x128::describe("f64-n64x128"),
+  };
+  *count = (int)(sizeof(v) / sizeof(v[0]));
+  return v;
+}
+
+const Variant* reduced_f64(int* count) {
+  static const Variant v[] = {
+      R64::describe("f64-n64-r48"),       R72::describe("f64-n72-r60"),
+      R80::describe("f64-n80-r60"),       R96::describe("f64-n96-r72"),
+      R108::describe("f64-n108-r80"),     R120::describe("f64-n120-r96"),
+      R128::describe("f64-n128-r96"),     R64x128::describe("f64-n64x128-r48x96"),
   };
   *count = (int)(sizeof(v) / sizeof(v[0]));
   return v;

@@ -195,9 +195,12 @@ template <> struct HalfZ<64> { using type = Sched<8, 8>; };
 // XD (with HY, half-width input too): the W columns of a brick are the even
 // x = 2x' (psi read over 2W columns), stored as column x' of rows of N / 2
 // points (a quarter plane).
+// GO, GOZ (reduced pair grids, see ReducedPipeline): psi lies on an N x N x NZ
+// sampling grid and the pair grids have GO x GO x GOZ points: frequency k goes
+// to plane k or, negative, k + GOZ - NZ, as N x N points at the plane's start.
 template <typename T, int N, int W, int NT, int TT, class SZF, bool PIL, bool SCR, int NZ = N,
           bool HZ = false, class SZH = typename HalfZ<NZ / 2>::type, bool HY = false,
-          bool XD = false>
+          bool XD = false, int GO = 0, int GOZ = 0>
 __global__ void __launch_bounds__(NT) k_pair_fwd(PassGroup grp) {
   int sys_ = 0;
   const int lg_ = grp.locate(xcd_remap(blockIdx.x, gridDim.x), sys_);
@@ -218,13 +221,17 @@ __global__ void __launch_bounds__(NT) k_pair_fwd(PassGroup grp) {
   // full planes: a brick is W consecutive points of the xy plane in storage
   // order (flat bricks, whole cache lines at any N); reduced planes: W
   // columns of one stored row
-  static_assert(HY || (N * N) % W == 0, "flat bricks tile the plane");
-  constexpr int BR = HY ? (N / 2) * NXB : N * N / W;  // bricks per tile pair
+  static_assert(HY || GO || (N * N) % W == 0, "flat bricks tile the plane");
+  static_assert(!GO || (!HZ && !HY && GO >= N && GOZ >= NZ), "reduced grids hold the samples");
+  constexpr int BR = HY ? (N / 2) * NXB : (N * N + W - 1) / W;  // bricks per tile pair
   constexpr int LIM = HY ? NXI : N * N;  // bound of x0 + m
   constexpr int P = ZL * W;
   constexpr int PT = (P + NT - 1) / NT;
   constexpr long long NR = (long long)NZ * N * N;
-  constexpr int ZSL = (ZL / RL) * N * N;  // offset between legs of a last-stage butterfly
+  constexpr int PA = GO ? GO * GO : N * N;            // points of a pair grid's plane
+  constexpr long long GNR = GO ? (long long)GOZ * PA : NR;  // and of a pair grid
+  constexpr int ZSL = (ZL / RL) * PA;  // offset between legs of a last-stage butterfly
+  constexpr int ZHI = (GO ? GOZ - ZL : NZ / 2) * PA;  // shift of the negative frequencies
   constexpr int ZS = HZ ? 2 : 1;         // z stride of the product points
   constexpr int YS = HY ? 2 : 1;         // y stride of the brick rows
   constexpr int XS = XD ? 2 : 1;         // x stride of the brick columns
@@ -257,7 +264,7 @@ __global__ void __launch_bounds__(NT) k_pair_fwd(PassGroup grp) {
   int offL[L::PER], gL[L::PER];
   bool vL[L::PER];
   unsigned kzL[L::PER];  // bit r: leg r (frequency j + r ZL / RL) lies on a kept kz plane
-  unsigned hiL[L::PER];  // HZ, bit r: leg r is a negative frequency (grid plane + NZ / 2)
+  unsigned hiL[L::PER];  // HZ, GO, bit r: leg r is a negative frequency (shifted by ZHI)
 #pragma unroll
   for (int i = 0; i < L::PER; ++i) {
     int m = 0, j = 0;
@@ -265,14 +272,14 @@ __global__ void __launch_bounds__(NT) k_pair_fwd(PassGroup grp) {
     gL[i] = m / W;
     const int mx = m - gL[i] * W;
     vL[i] = L::valid(tid, i) && (x0 + mx) < LIM;
-    offL[i] = vL[i] ? j * N * N + y * XST + x0 + mx : 0;
+    offL[i] = vL[i] ? j * PA + y * XST + x0 + mx : 0;
     kzL[i] = 0;
     hiL[i] = 0;
 #pragma unroll
     for (int r = 0; r < RL; ++r) {
       const int k = j + r * (ZL / RL);
       kzL[i] |= (kz_kept(k, ZL, a.kz_max) ? 1u : 0u) << r;
-      if constexpr (HZ) hiL[i] |= (2 * k >= ZL ? 1u : 0u) << r;
+      if constexpr (HZ || GO) hiL[i] |= (2 * k >= ZL ? 1u : 0u) << r;
     }
   }
 
@@ -358,12 +365,11 @@ __global__ void __launch_bounds__(NT) k_pair_fwd(PassGroup grp) {
       for (int i = 0; i < L::PER; ++i) {
         const bool use = gL[i] == 0 ? use0 : use1;
         if (vL[i] && use) {
-          cpx<T>* g = grids + (long long)(slot0 + gL[i]) * NR;
+          cpx<T>* g = grids + (long long)(slot0 + gL[i]) * GNR;
 #pragma unroll
           for (int r = 0; r < RL; ++r)
             if ((kzL[i] >> r) & 1u)
-              g[offL[i] + r * ZSL + (((hiL[i] >> r) & 1u) ? (NZ / 2) * N * N : 0)] =
-                  out[i * RL + r];
+              g[offL[i] + r * ZSL + (((hiL[i] >> r) & 1u) ? ZHI : 0)] = out[i * RL + r];
         }
       }
     });
@@ -812,9 +818,12 @@ constexpr int plane_waves_per_eu() {
 // run at length N / 2 (the same half-length schedule) and place half-length
 // frequency k in column k below N / 4, else k + N / 2; the inverse x
 // transforms read the band's columns and take zeros elsewhere.
+// NF: length of the forward transforms of such planes: N / 2, or the sampling
+// length of reduced pair grids (rows of NF points, contiguous), with NF / 2
+// in place of N / 4 above.
 template <typename T, int N, int NT, class SXF, class SXI, class SYF, class SYI, bool SW = false,
           bool PP = false, int NZ = N, int QB = 0, bool GM = false, bool HY = false,
-          class SYH = SYF, bool XD = false>
+          class SYH = SYF, bool XD = false, int NF = N / 2>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves_per_eu<T, N, NT>())))
 k_plane_conv(PassGroup grp) {
   int sys_ = 0;
@@ -822,12 +831,13 @@ k_plane_conv(PassGroup grp) {
   const PassArgs& a = grp.a[sys_];
   static_assert(!SW || N % 8 == 0, "swizzle needs whole blocks of 8");
   static_assert(QB == 0 || (!SW && 2 * QB + 1 < N), "band columns: no swizzle, inside the row");
-  static_assert(!HY || (QB > 0 && N % 4 == 0), "half-height planes come with band columns");
-  static_assert(!XD || (HY && QB == N / 4), "half-width input comes with half-height input");
+  static_assert(!HY || (QB > 0 && NF % 2 == 0), "half-height planes come with band columns");
+  static_assert(!XD || (HY && QB == NF / 2), "half-width input comes with half-height input");
+  static_assert(NF == N / 2 || (XD && NF < N), "sampled planes are decimated along x and y");
   constexpr int P = N + 1;
-  constexpr int NI = HY ? N / 2 : N;  // rows of the plane's input
-  constexpr int NXI = XD ? N / 2 : N;  // points per input row
-  constexpr int XST = reduced_row_stride<N, HY, XD>();  // input row stride
+  constexpr int NI = HY ? NF : N;  // rows of the plane's input
+  constexpr int NXI = XD ? NF : N;  // points per input row
+  constexpr int XST = NF == N / 2 ? reduced_row_stride<N, HY, XD>() : NF;  // input row stride
   constexpr int MB = QB ? 2 * QB + 1 : N;
   using GX = Geom<T, N, N, NT, false, 1, P, SW ? 1 : 0>;  // rows: sequence m = y, element n = x
   using GXF = Geom<T, NXI, NI, NT, false, 1, P, SW ? 1 : 0>;  // the input rows
@@ -1556,6 +1566,97 @@ struct FusedPipeline {
     v.qb = QB;
     v.hy = HYOK;
     v.xd = HYOK;
+    v.plane_lds = lds;
+    v.pair_fwd = &pair_fwd;
+    v.plane = &plane;
+    v.inv_acc = &inv_acc;
+    v.inv_energy = &inv_energy;
+    v.prepare = &prepare;
+    return v;
+  }
+};
+
+// Band-limited plans whose grid oversamples the pair densities twofold along
+// every axis (pair band |k| <= kmax with 2 kmax + 1 <= N / 2, so orbitals
+// within |m| <= kmax / 2): the pair pipeline runs on grids of its own instead
+// of the caller's N^3.
+//   forward: the densities' band fits the NF = N / 2 points of every other
+//     sample, which determine it exactly;
+//   inverse: K psi_a is a sum of products v_ab psi_b of band kmax + kmax / 2,
+//     which NI >= 3 kmax + 1 points resolve (NI is 3/4 of N, or the next
+//     length with a schedule).
+// The plan samples the orbitals on both grids once per call (psi[::2] and a
+// band-limited interpolation to NI^3) and interpolates K psi back to N^3; per
+// pair only NF^3 points are formed and transformed forward, and NI^3 points
+// back and accumulated, where the full pipeline moves N^3.
+// NFZ, NIZ: the same along z (slab cells).
+template <typename T, int NF, int NI, int W, int TT, int NTQ, class SXI, class SYI, class SZI,
+          int NTF, int NTI, bool PJL, bool PF, int FLI = 0, int NFZ = NF, int NIZ = NI>
+struct ReducedPipeline {
+  using SXF = typename HalfZ<NF>::type;   // forward x and y
+  using SZF = typename HalfZ<NFZ>::type;  // forward z
+  static constexpr int QB = NF / 2;
+  static constexpr bool FLB = FLI != 0;
+  static constexpr int NGI = FLI == 4 ? 4 : 2;
+  static constexpr size_t lds = (size_t)NI * (NI + 1) * sizeof(cpx<T>);
+  static constexpr auto plane_kernel =
+      &k_plane_conv<T, NI, NTQ, SXF, SXI, SXF, SYI, false, false, NIZ, QB, false, true, SXF, true,
+                    NF>;
+  template <bool SCR>
+  static void fwd_launch(const PassGroup& g, int nb, hipStream_t s) {
+    hipLaunchKernelGGL((k_pair_fwd<T, NF, W, NTF, TT, SZF, false, SCR, NFZ, false, void, false,
+                                   false, NI, NIZ>),
+                       dim3(nb), dim3(NTF), 0, s, g);
+  }
+  static void pair_fwd(const PassGroup& g, int nb, hipStream_t s) {
+    if (g.a[0].perm)
+      fwd_launch<true>(g, nb, s);
+    else
+      fwd_launch<false>(g, nb, s);
+  }
+  static void plane(const PassGroup& g, int nb, hipStream_t s) {
+    hipLaunchKernelGGL(plane_kernel, dim3(nb), dim3(NTQ), lds, s, g);
+  }
+  // at most two thirds of the planes are kept: pruned loads are skipped
+  template <bool ACC, bool SCR>
+  static void inv_launch(const PassGroup& g, int nb, hipStream_t s) {
+    hipLaunchKernelGGL((k_inv_acc<T, NI, W, NTI, TT, SZI, ACC, PJL, PF, SCR, NIZ, 2, FLB, NGI>),
+                       dim3(nb), dim3(NTI), 0, s, g);
+  }
+  template <bool ACC>
+  static void inv_pass(const PassGroup& g, int nb, hipStream_t s) {
+    if (g.a[0].perm)
+      inv_launch<ACC, true>(g, nb, s);
+    else
+      inv_launch<ACC, false>(g, nb, s);
+  }
+  static void inv_acc(const PassGroup& g, int nb, hipStream_t s) { inv_pass<true>(g, nb, s); }
+  static void inv_energy(const PassGroup& g, int nb, hipStream_t s) { inv_pass<false>(g, nb, s); }
+  static hipError_t prepare() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(plane_kernel),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  }
+  static Variant describe(const char* name) {
+    Variant v{};
+    v.name = name;
+    v.n = NI;
+    v.nz = NIZ;
+    v.nf = NF;
+    v.nfz = NFZ;
+    v.prec = sizeof(T) == 8 ? 1 : 0;
+    v.brick = W;
+    v.tile = TT;
+    v.max_rows = kMaxRows;
+    v.nt_fwd = NTF;
+    v.nt_acc = NTI;
+    v.nt_plane = NTQ;
+    fill_radices(v.zf, v.nzf, SZF{});
+    fill_radices(v.zi, v.nzi, SZI{});
+    fill_radices(v.xf, v.nxf, SXF{});
+    fill_radices(v.xi, v.nxi, SXI{});
+    fill_radices(v.yf, v.nyf, SXF{});
+    fill_radices(v.yi, v.nyi, SYI{});
+    fill_radices(v.zh, v.nzh, SXF{});
     v.plane_lds = lds;
     v.pair_fwd = &pair_fwd;
     v.plane = &plane;

@@ -70,6 +70,15 @@ namespace {
 struct SystemPlan {
   hfx_system sys;
   const Variant* var = nullptr;
+  // reduced pair grids (see reduced_variant): the pipeline the exchange calls
+  // run instead of var's, on pair grids of rvar->n^2 x rvar->nz points; null
+  // otherwise
+  const Variant* rvar = nullptr;
+  const Variant* pv() const { return rvar ? rvar : var; }
+  long long grid_points() const { return rvar ? (long long)rvar->n * rvar->n * rvar->nz : nr; }
+  long long sample_points() const {
+    return rvar ? (long long)rvar->nf * rvar->nf * rvar->nfz : nr;
+  }
   int n = 0;
   long long nr = 0;
   double dv = 0.0;
@@ -90,8 +99,14 @@ struct SystemPlan {
   void* tw[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   TileDesc* d_tiles = nullptr;
   int* d_active = nullptr;
+  // resampling matrices of reduced plans: psi to the pair grid (x and y, z),
+  // K psi back (x and y, z)
+  void* d_rs[4] = {nullptr, nullptr, nullptr, nullptr};
   void* d_zero = nullptr;  // kZeroBytes of zeros: what pruned kz planes read as (band-limited plans)
   // offsets inside the caller's workspace
+  // reduced plans: psi at the sampling points (float64; float32 plans also
+  // float32 at off_psi32), psi and K psi on the pair grid
+  size_t off_samp = 0, off_psig = 0, off_kpsig = 0;
   size_t off_psi32 = 0, off_grids = 0, off_partials = 0, off_gemm = 0, off_ortho = 0;
   // K psi staging of the gradient (float32 plans) and of hfx_exchange_matrix
   // (both precisions): n_orb x N_r values of the working precision
@@ -275,11 +290,34 @@ bool parse_count(const std::string& v, long long* out) {
   return true;
 }
 
+// The reduced pipeline of a system, or null: the pair densities' band (k_max
+// along each axis, twice the orbitals') fits half the points of every axis,
+// so every other sample carries it, and K psi, of band 3/2 k_max, fits the
+// reduced pair grid.  Systems whose plan names a kernel configuration other
+// than the grid's default keep that one.
+const Variant* reduced_variant(const SystemPlan& sp, int prec) {
+  if (sp.var != find_variant(sp.sys.n[0], sp.sys.n[2], prec)) return nullptr;
+  int count = 0;
+  const Variant* v = prec == HFX_FP64 ? reduced_f64(&count) : reduced_f32(&count);
+  auto fits = [](int k, int nf, int ni) { return 2 * (long long)k + 1 <= nf && 3 * (long long)k + 1 <= ni; };
+  for (int i = 0; i < count; ++i)
+    if (2 * v[i].nf == sp.sys.n[0] && 2 * v[i].nfz == sp.sys.n[2] &&
+        fits(sp.kx_max, v[i].nf, v[i].n) && fits(sp.ky_max, v[i].nf, v[i].n) &&
+        fits(sp.kz_max, v[i].nfz, v[i].nz))
+      return &v[i];
+  return nullptr;
+}
+
 // Workgroups of pass 3 (and of pass 1 on full planes) per tile pair: flat
 // bricks of `brick` consecutive points of the n x n plane (the kernels assert
 // that they tile it).
 int bricks_per_tile(const Variant* v) {
   return v->n * v->n / v->brick;
+}
+// Workgroups of pass 1 per tile pair on the sampling points of reduced pair
+// grids (the last brick may be partly off the plane).
+int sample_bricks(const Variant* v) {
+  return (v->nf * v->nf + v->brick - 1) / v->brick;
 }
 
 // Whether the forward z transform of pair_fwd runs at half length: pair
@@ -307,9 +345,9 @@ bool half_x(const Variant* v, int kx_max, int ky_max) {
 ScheduleShape shape_of(const SystemPlan& sp) {
   ScheduleShape sh;
   sh.n_orb = sp.sys.n_orb;
-  sh.tile = sp.var->tile;
+  sh.tile = sp.pv()->tile;
   sh.rows = sp.rows;
-  sh.bricks = bricks_per_tile(sp.var);
+  sh.bricks = bricks_per_tile(sp.pv());
   sh.shard = sp.shard;
   sh.shards = sp.shards;
   return sh;
@@ -418,6 +456,10 @@ hfx_status validate_system(const hfx_system& s, int idx) {
 
 void free_system(SystemPlan& sp) {
   if (sp.vtab) (void)hipFree(sp.vtab);
+  for (auto& p : sp.d_rs) {
+    if (p) (void)hipFree(p);
+    p = nullptr;
+  }
   for (auto& p : sp.tw)
     if (p) (void)hipFree(p);
   if (sp.d_tiles) (void)hipFree(sp.d_tiles);
@@ -561,7 +603,8 @@ struct SysCall {
 // for bit (every workgroup does the same work).  acc: accumulate K psi.
 hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* ws,
                         hipStream_t st, bool acc) {
-  const Variant* v = calls[0].sp->var;
+  const Variant* v = calls[0].sp->pv();
+  const bool reduced = calls[0].sp->rvar != nullptr;
   const size_t elem = plan->prec == HFX_FP64 ? 8 : 4;
   const int nc = (int)calls.size();
   std::vector<PassArgs> args(nc);
@@ -570,7 +613,7 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
   // all its members in one launch each (per-system launches on one stream
   // would serialise many small launches); results are those of the
   // per-system launches bit for bit.
-  const bool joint = nc > 1;
+  const bool joint = nc > 1 && !reduced;
   if (joint) {
     double orbs = 0.0, mean_flops = 0.0;
     for (const SysCall& c : calls) {
@@ -627,7 +670,25 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     const double* psi = calls[c].psi;
     const void* psi_w = psi;
     const double orb_pts = (double)sp.sys.n_orb * (double)sp.nr;
-    if (joint) {
+    if (reduced) {
+      // the orbitals at the sampling points and on the pair grid (the pair-grid
+      // buffer is free until pass 1 and serves as scratch)
+      const int n = sp.sys.n[0], nz = sp.sys.n[2], no = sp.sys.n_orb;
+      double* samp = reinterpret_cast<double*>(ws + sp.off_samp);
+      float* samp32 =
+          plan->prec == HFX_FP32 ? reinterpret_cast<float*>(ws + sp.off_psi32) : nullptr;
+      Bracket br(plan, HFX_PASS_STAGE, st);
+      launch_decimate(psi, no, n, nz, samp, samp32, st);
+      const double *rx = static_cast<double*>(sp.d_rs[0]), *rz = static_cast<double*>(sp.d_rs[1]);
+      if (samp32)
+        launch_resample(psi, reinterpret_cast<float*>(ws + sp.off_psig), no, n, nz, v->n, v->nz,
+                        rx, rz, ws + sp.off_grids, sp.grid_bytes, st);
+      else
+        launch_resample(psi, reinterpret_cast<double*>(ws + sp.off_psig), no, n, nz, v->n, v->nz,
+                        rx, rz, ws + sp.off_grids, sp.grid_bytes, st);
+      br.done(orb_pts * 12.0, 0.0);
+      psi_w = samp32 ? static_cast<const void*>(samp32) : samp;
+    } else if (joint) {
       psi_w = plan->prec == HFX_FP32 ? static_cast<const void*>(ws + sp.off_psi32) : psi;
     } else if (plan->prec == HFX_FP32) {
       float* p32 = reinterpret_cast<float*>(ws + sp.off_psi32);
@@ -647,7 +708,10 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       double* mu = reinterpret_cast<double*>(ws + sp.off_mean);
       double* part = reinterpret_cast<double*>(ws + sp.off_gemm);
       Bracket br(plan, HFX_PASS_CONTRACT, st);
-      launch_xtx_f64(psi, psi, sp.sys.n_orb, sp.nr, 1.0 / (double)sp.nr, part, mu, st);
+      // the sampling points carry the products' band, so their mean is exact
+      const double* ps = reduced ? reinterpret_cast<const double*>(ws + sp.off_samp) : psi;
+      const long long np = sp.sample_points();
+      launch_xtx_f64(ps, ps, sp.sys.n_orb, np, 1.0 / (double)np, part, mu, st);
       // screened pairs contribute no G = 0 energy either
       if (sp.d_keep) launch_mask(mu, sp.d_keep, (size_t)sp.sys.n_orb * sp.sys.n_orb, st);
       br.done(orb_pts * 8.0, 2.0 * (double)sp.sys.n_orb * orb_pts);
@@ -655,13 +719,14 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     }
     if (acc && !joint) {
       Bracket br(plan, HFX_PASS_ZERO, st);
-      launch_zero(calls[c].kpsi, (size_t)sp.sys.n_orb * sp.nr * elem, st);
+      launch_zero(reduced ? static_cast<void*>(ws + sp.off_kpsig) : calls[c].kpsi,
+                  (size_t)sp.sys.n_orb * sp.grid_points() * elem, st);
       br.done(orb_pts * elem, 0.0);
     }
     PassArgs& a = args[c];
     a = PassArgs{};
     a.psi = psi_w;
-    a.kpsi = calls[c].kpsi;
+    a.kpsi = reduced ? static_cast<void*>(ws + sp.off_kpsig) : calls[c].kpsi;
     a.vtab = sp.vtab;
     a.tw_zf = sp.tw[0];
     a.tw_zi = sp.tw[1];
@@ -733,7 +798,8 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       a.part_base = b.part_base;
       g.a[(int)who.size()] = a;
       who.push_back(c);
-      const double nr = (double)sp.nr;
+      const double nr = (double)sp.grid_points();
+      const double ns = (double)sp.sample_points() / nr;  // share pass 1 forms (reduced grids)
       // share of the grid on kept kz planes (pair-grid traffic of the passes)
       const double kzf = (double)kz_planes(nz, sp.kz_max) / nz;
       // FFT flops per complex grid and axis pass: 5 N_r log2(N) (radix-2 count)
@@ -760,16 +826,17 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       }
       const double grids = (double)b.n_active;
       const int kp = kz_planes(nz, sp.kz_max);
-      nb_fwd.push_back(b.n_tiles * (xd ? (n / 2) * nxbh : hy ? (n / 2) * nxb : br));
-      // a half-length forward z transform reads the orbitals on even z only,
-      // half-height input on even y only (and stores half the rows);
-      // half-width input stores half the columns (its orbital reads, every
-      // other point of a row, still move whole rows)
-      by_fwd += orbs * nr * elem * (half_z(v, sp.kz_max) ? 0.5 : 1.0) * yf +
-                grids * nr * ce * kzf * yf * xf;
-      fl_fwd += grids * fft_z * yf * xf;
+      nb_fwd.push_back(b.n_tiles * (reduced ? sample_bricks(v)
+                                    : xd    ? (n / 2) * nxbh
+                                    : hy    ? (n / 2) * nxb
+                                            : br));
+      // share of a kept plane's points that pass 1 stores
+      const double pf = reduced ? (double)v->nf * v->nf / ((double)n * n) : yf * xf;
+      by_fwd += orbs * nr * elem * (reduced ? ns : (half_z(v, sp.kz_max) ? 0.5 : 1.0) * yf) +
+                grids * nr * ce * kzf * pf;
+      fl_fwd += grids * fft_z * (reduced ? ns : yf * xf);
       nb_pl.push_back(b.n_active * kp);
-      by_pl += grids * nr * ce * (1.0 + yf * xf) * kzf;
+      by_pl += grids * nr * ce * (1.0 + pf) * kzf;
       fl_pl += grids * fft_axis * 4.0 * kzf;
       nb_row.push_back(b.n_active * ((kp * n + v->rows_per_wg - 1) / std::max(v->rows_per_wg, 1)));
       by_row += grids * nr * ce * 2.0 * kzf;
@@ -803,6 +870,8 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       launch(v->cols_conv, nb_col, HFX_PASS_COLS_CONV, by_col, fl_col);
       launch(v->rows_inv, nb_row, HFX_PASS_ROWS_INV, by_row, fl_row);
     }
+    if (reduced)  // pass 3 takes the orbitals on the pair grid
+      for (int i = 0; i < g.count; ++i) g.a[i].psi = ws + calls[who[i]].sp->off_psig;
     if (two && k > 0) HIP_TRY(hipStreamWaitEvent(bs, sp0.ev_acc[q ^ 1], 0));
     if (acc)
       launch(v->inv_acc, nb_inv, HFX_PASS_INV_ACC, by_inv, fl_inv);
@@ -814,6 +883,23 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     HIP_TRY(hipEventRecord(sp0.ev_join, sp0.bstream));
     HIP_TRY(hipStreamWaitEvent(st, sp0.ev_join, 0));
   }
+  if (reduced && acc)
+    for (int c = 0; c < nc; ++c) {
+      // K psi back on the caller's grid; the pair grids are free again
+      SystemPlan& sp = *calls[c].sp;
+      const int n = sp.sys.n[0], nz = sp.sys.n[2], no = sp.sys.n_orb;
+      const double *rx = static_cast<double*>(sp.d_rs[2]), *rz = static_cast<double*>(sp.d_rs[3]);
+      Bracket bk(plan, HFX_PASS_STAGE, st);
+      if (plan->prec == HFX_FP32)
+        launch_resample(reinterpret_cast<const float*>(ws + sp.off_kpsig),
+                        static_cast<float*>(calls[c].kpsi), no, v->n, v->nz, n, nz, rx, rz,
+                        ws + sp.off_grids, sp.grid_bytes, st);
+      else
+        launch_resample(reinterpret_cast<const double*>(ws + sp.off_kpsig),
+                        static_cast<double*>(calls[c].kpsi), no, v->n, v->nz, n, nz, rx, rz,
+                        ws + sp.off_grids, sp.grid_bytes, st);
+      bk.done((double)no * ((double)sp.nr + (double)sp.grid_points()) * elem, 0.0);
+    }
   for (int c = 0; c < nc; ++c) {
     if (!calls[c].ex) continue;
     SystemPlan& sp = *calls[c].sp;
@@ -821,7 +907,7 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     const double om = sp.dv * (double)sp.nr;
     // the G = 0 energy of the means is not pair work: added by group 0 only
     const bool dc = sp.shard == 0;
-    launch_energy_reduce(args[c].partials, sp.n_partials, -0.5 * sp.dv,
+    launch_energy_reduce(args[c].partials, sp.n_partials, -0.5 * om / (double)sp.grid_points(),
                          dc ? args[c].mean : nullptr, sp.sys.n_orb,
                          dc ? -0.5 * om * sp.v0 : 0.0, calls[c].ex, st);
     bk.done((double)sp.n_partials * 8.0, 0.0);
@@ -834,7 +920,7 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
 long long largest_launch(const SystemPlan& sp) {
   long long m = 0;
   for (const Batch& b : sp.batches) m = std::max<long long>(m, b.n_tiles);
-  return m * bricks_per_tile(sp.var);
+  return m * bricks_per_tile(sp.pv());
 }
 
 // Systems whose pass launches stay below this many workgroups (two per
@@ -859,14 +945,14 @@ std::vector<std::vector<int>> size_classes(hfx_plan plan) {
     bool placed = false;
     const bool groupable =
         plan->group == 1 || (plan->group < 0 && largest_launch(sp) < kGroupBelowWorkgroups);
-    if (groupable && sp.nstreams == 1 && !sp.var->persistent)
+    if (groupable && sp.nstreams == 1 && !sp.pv()->persistent)
       for (auto& c : out) {
         const SystemPlan& f = plan->sys[c[0]];
         const bool fg =
             plan->group == 1 || (plan->group < 0 && largest_launch(f) < kGroupBelowWorkgroups);
-        if ((int)c.size() < kMaxGroup && fg && f.var == sp.var && f.kz_max == sp.kz_max &&
+        if ((int)c.size() < kMaxGroup && fg && f.pv() == sp.pv() && f.kz_max == sp.kz_max &&
             (f.d_keep != nullptr) == (sp.d_keep != nullptr) && f.nstreams == 1 &&
-            !f.var->persistent) {
+            !f.pv()->persistent) {
           c.push_back(i);
           placed = true;
           break;
@@ -1312,7 +1398,6 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
       r = std::min(r, sp.var->max_rows);
       sp.rows = std::max(t, r / t * t);
     }
-    schedule_all_pairs(sp, sp.tiles_cap);
     sp.kz_max = kz_max_for(ecut, sys[i].L[2]);
     sp.kx_max = kz_max_for(ecut, sys[i].L[0]);
     sp.ky_max = kz_max_for(ecut, sys[i].L[1]);
@@ -1322,25 +1407,58 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
     orb_off += sys[i].n_orb;
     psi_off += (long long)sys[i].n_orb * sp.nr;
     m_off += (long long)sys[i].n_orb * sys[i].n_orb;
-    // workspace layout of this system
-    sp.off_psi32 = off;
-    if (precision == HFX_FP32) off = align_up(off + (size_t)sys[i].n_orb * sp.nr * 4);
-    sp.nstreams = (sp.batches.size() > 1 && batch_streams == 2) ? 2 : 1;
-    sp.off_grids = off;
-    sp.grid_bytes = align_up((size_t)sp.slots_per_batch * sp.nr * 2 * elem);
-    off = align_up(off + sp.grid_bytes * sp.nstreams);
-    sp.off_partials = off;
-    {
-      // room for every tile pair of the system: a screened schedule (or
-      // another virtual group's share) never needs more
-      const long long nb = (sys[i].n_orb + sp.var->tile - 1) / sp.var->tile;
-      const long long all = nb * (nb + 1) / 2 * bricks_per_tile(sp.var);
-      off = align_up(off + (size_t)std::max(sp.n_partials, all) * 8);
+    // schedule and workspace layout of this system (the regions the energy
+    // and K psi calls use) from offset `from`; returns its end
+    auto layout = [&](size_t from) {
+      size_t o = from;
+      auto take = [&](size_t* at, size_t bytes) {
+        *at = o;
+        o = align_up(o + bytes);
+      };
+      const size_t no = (size_t)sys[i].n_orb;
+      schedule_all_pairs(sp, sp.tiles_cap);
+      if (sp.rvar) {
+        take(&sp.off_samp, no * sp.sample_points() * 8);
+        take(&sp.off_psig, no * sp.grid_points() * elem);
+        take(&sp.off_kpsig, no * sp.grid_points() * elem);
+      }
+      take(&sp.off_psi32, precision == HFX_FP32 ? no * sp.sample_points() * 4 : 0);
+      sp.nstreams = (sp.batches.size() > 1 && batch_streams == 2) ? 2 : 1;
+      sp.grid_bytes = align_up((size_t)sp.slots_per_batch * sp.grid_points() * 2 * elem);
+      if (sp.rvar) {
+        // also scratch of the resampling (one orbital at least)
+        const Variant* r = sp.rvar;
+        sp.grid_bytes = std::max(
+            sp.grid_bytes,
+            align_up(std::max(resample_tmp_bytes(sp.n, sys[i].n[2], r->n, r->nz),
+                              resample_tmp_bytes(r->n, r->nz, sp.n, sys[i].n[2]))));
+      }
+      take(&sp.off_grids, sp.grid_bytes * sp.nstreams);
+      {
+        // room for every tile pair of the system: a screened schedule (or
+        // another virtual group's share) never needs more
+        const long long nb = (sys[i].n_orb + sp.pv()->tile - 1) / sp.pv()->tile;
+        const long long all = nb * (nb + 1) / 2 * bricks_per_tile(sp.pv());
+        take(&sp.off_partials, (size_t)std::max(sp.n_partials, all) * 8);
+      }
+      take(&sp.off_gemm, gemm_partial_bytes(sys[i].n_orb, sp.nr));
+      take(&sp.off_mean, precision == HFX_FP32 ? no * no * 8 : 0);
+      return o;
+    };
+    size_t end = layout(off);
+    if (const Variant* r = reduced_variant(sp, precision)) {
+      // its orbital copies must not need more workspace than the smaller
+      // pair grids free (many orbitals with few, capped tiles per batch)
+      sp.rvar = r;
+      const size_t rend = layout(off);
+      if (rend > end) {
+        sp.rvar = nullptr;
+        end = layout(off);
+      } else {
+        end = rend;
+      }
     }
-    sp.off_gemm = off;
-    off = align_up(off + gemm_partial_bytes(sys[i].n_orb, sp.nr));
-    sp.off_mean = off;
-    if (precision == HFX_FP32) off = align_up(off + (size_t)sys[i].n_orb * sys[i].n_orb * 8);
+    off = end;
   }
   // Everything the energy and K psi calls use comes first (all systems);
   // the regions only the other calls use follow.
@@ -1373,25 +1491,48 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
     return cleanup(fail(HFX_EDEVICE, "no HIP device available"));
   {
     hipError_t e = prepare_apply_left();
+    if (e == hipSuccess) e = prepare_resample();
     if (e != hipSuccess)
       return cleanup(fail(HFX_EDEVICE, std::string("kernel set-up: ") + hipGetErrorString(e)));
   }
   for (auto& sp : p->sys) {
     hfx_status s;
-    if (sp.var->prepare) {
-      hipError_t e = sp.var->prepare();
+    if (sp.pv()->prepare) {
+      hipError_t e = sp.pv()->prepare();
       if (e != hipSuccess)
         return cleanup(fail(HFX_EDEVICE, std::string("kernel set-up: ") + hipGetErrorString(e)));
     }
     // a hybrid mixing fraction scales the kernel, hence E_x, K psi, M and
     // the gradient alike
     sp.v0 = mix * kernel_g0(sp.sys);
+    const Variant* v = sp.pv();
+    // on reduced grids the forward transforms sum sample_points() values
+    hfx_system gs = sp.sys;
+    double vscale = mix;
+    if (sp.rvar) {
+      gs.n[0] = gs.n[1] = v->n;
+      gs.n[2] = v->nz;
+      vscale *= (double)sp.grid_points() / (double)sp.sample_points();
+    }
     if (precision == HFX_FP64)
-      s = upload(kernel_table<double>(sp.sys, false, mix), &sp.vtab);
+      s = upload(kernel_table<double>(gs, false, vscale), &sp.vtab);
     else
-      s = upload(kernel_table<float>(sp.sys, true, mix), &sp.vtab);
+      s = upload(kernel_table<float>(gs, true, vscale), &sp.vtab);
     if (s != HFX_OK) return cleanup(s);
-    const Variant* v = sp.var;
+    if (sp.rvar) {
+      // bands: orbitals |m| <= kmax / 2, K psi |m| <= 3/2 kmax, for the
+      // largest kmax the sampling points allow
+      const int n = sp.sys.n[0], nz = sp.sys.n[2];
+      const int bx = (v->nf - 1) / 4, bz = (v->nfz - 1) / 4;
+      const int from[4] = {n, nz, v->n, v->nz}, to[4] = {v->n, v->nz, n, nz};
+      const int band[4] = {bx, bz, 3 * bx, 3 * bz};
+      for (int k = 0; k < 4; ++k) {
+        std::vector<double> m(resample_entries(from[k], to[k]));
+        resample_matrix(from[k], to[k], band[k], m.data());
+        s = upload(m, &sp.d_rs[k]);
+        if (s != HFX_OK) return cleanup(s);
+      }
+    }
     const int* rs[6] = {v->zf, v->zi, v->xf, v->xi, v->yf, v->yi};
     const int cs[6] = {v->nzf, v->nzi, v->nxf, v->nxi, v->nyf, v->nyi};
     for (int k = 0; k < 6; ++k) {
@@ -1735,6 +1876,9 @@ const char* hfx_plan_describe(hfx_plan plan, int system) {
                                         : std::string()) +
                   (half_y(v, sp.kx_max, sp.ky_max) ? " y_rows=half" : std::string()) +
                   (half_x(v, sp.kx_max, sp.ky_max) ? " x_cols=half" : std::string()) +
+                  (sp.rvar ? " pair_grid=" + std::to_string(sp.rvar->nf) + "->" +
+                                 std::to_string(sp.rvar->n)
+                           : std::string()) +
                   " tiles_per_batch=" + std::to_string(sp.tiles_per_batch) +
                   " batches=" + std::to_string(sp.batches.size()) +
                   " streams=" + std::to_string(sp.nstreams) +

@@ -127,6 +127,7 @@ struct Variant {
   const char* name;
   int n;           // grid points along x and y
   int nz;          // grid points along z (n for cubic grids)
+  int nf, nfz;     // reduced pair grids: sampling points of the forward transforms, else 0
   int prec;        // 0 float32, 1 float64
   int brick;       // pencil width W (x values per workgroup)
   int tile;        // orbital tile T (columns of a tile pair)
@@ -158,6 +159,28 @@ struct Variant {
 
 const Variant* variants_f32(int* count);
 const Variant* variants_f64(int* count);
+// Reduced pair grids of band-limited plans (nf = half the caller's grid).
+const Variant* reduced_f32(int* count);
+const Variant* reduced_f64(int* count);
+
+// Band-limited resampling (resample.hpp).  decimate: psi (n x n x nz per
+// orbital, x fastest) at its even points, as float64 and, when out32 is not
+// null, as float32.
+void launch_decimate(const double* psi, int n_orb, int n, int nz, double* out64, float* out32,
+                     hipStream_t s);
+// Interpolation matrix b points <- a points of a periodic band |k| <= kmax, in
+// the order of the kernels' matrix fragments (host; resample_entries values).
+size_t resample_entries(int a, int b);
+void resample_matrix(int a, int b, int kmax, double* out);
+// n_orb grids a x a x az -> b x b x bz (float32 sources: b > a) with the
+// matrices rx (x and y) and rz, through tmp (tmp_bytes; at least
+// resample_tmp_bytes for one orbital).
+size_t resample_tmp_bytes(int a, int az, int b, int bz);
+hipError_t prepare_resample();
+template <typename S, typename O>
+void launch_resample(const S* in, O* out, int n_orb, int a, int az, int b, int bz,
+                     const double* rx, const double* rz, void* tmp, size_t tmp_bytes,
+                     hipStream_t s);
 
 // Elementwise helpers (exchange_common.hip)
 void launch_cast_f64_f32(const double* in, float* out, size_t n, hipStream_t s);
