@@ -240,11 +240,15 @@ __global__ void __launch_bounds__(NT) k_pair_fwd(PassGroup grp) {
   __shared__ T mul[kMaxRows * TT];  // pair-density means of the tile, [a][b]
   __shared__ T pil[PIL ? TT * PT * NT : 1];  // psi of the I block, [a][k][tid]
   const int tid = threadIdx.x;
-  const int lg = lg_;
+  // row chunk of the tile pair (neighbouring workgroups share a brick's psi_J)
+  const int lg = lg_ / a.fwd_chunks, chunk = lg_ - lg * a.fwd_chunks;
   const int t = lg / BR, br = lg - t * BR;
   // y: the stored row (read at YS y); flat bricks: y = 0, x0 = flat offset
   const int y = HY ? br / NXB : 0, x0 = HY ? (br - y * NXB) * W : br * W;
   const TileDesc td = a.tiles[t];
+  const int ia_begin = chunk * a.fwd_rows;
+  const int ia_end = ia_begin + a.fwd_rows < td.nI ? ia_begin + a.fwd_rows : td.nI;
+  if (ia_begin >= ia_end) return;  // a tile pair with fewer rows
   const T* __restrict__ psi = static_cast<const T*>(a.psi);
   stage_twiddles<T, SZ, NT>(twl, HZ ? a.tw_zh : a.tw_zf, tid);
   stage_means<T, TT, NT, SCR>(mul, a, td, 1.0, tid);
@@ -319,7 +323,7 @@ __global__ void __launch_bounds__(NT) k_pair_fwd(PassGroup grp) {
   });
   __syncthreads();
 
-  for (int ia = 0; ia < td.nI; ++ia) {
+  for (int ia = ia_begin; ia < ia_end; ++ia) {
     if constexpr (SCR) {
       if (!((rows >> ia) & 1u)) continue;  // no evaluated pair in this row
     }

@@ -342,6 +342,25 @@ bool half_x(const Variant* v, int kx_max, int ky_max) {
   return v->xd && half_y(v, kx_max, ky_max) && kx_max <= (v->n / 2 - 1) / 2;
 }
 
+// Workgroups of a pass 1 launch (two 256-thread workgroups per compute unit)
+// below which the rows of its tile pairs are dealt to several workgroups.
+constexpr int kFwdWorkgroups = 512;
+
+// Row chunks per tile pair of a pass 1 launch of nb workgroups (one per tile
+// pair and brick): doubled until the launch has kFwdWorkgroups, down to two
+// rows per workgroup.  A small launch is bound by the chain of its rows'
+// transforms; each chunk reads psi_J and sets up again, which launches that
+// fill the device should not pay for.  Measured (one call, us; never split /
+// 512 / 1024 workgroups): 8 orbitals on 24^3, float64, 54.4 / 46.0 / 46.1; 13
+// on 64^3 237 / 218 / 215; 64 on 64^3 at 5 Ha 1417 / 1255 / 1223; two
+// channels of 21 and 18 on 64^2 x 128, whose streams overlap, 1529 / 1489 /
+// 1556.
+int fwd_chunks(long long nb, int rows) {
+  int c = 1;
+  while (nb * c < kFwdWorkgroups && rows / (2 * c) >= 2) c *= 2;
+  return c;
+}
+
 ScheduleShape shape_of(const SystemPlan& sp) {
   ScheduleShape sh;
   sh.n_orb = sp.sys.n_orb;
@@ -826,10 +845,22 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       }
       const double grids = (double)b.n_active;
       const int kp = kz_planes(nz, sp.kz_max);
-      nb_fwd.push_back(b.n_tiles * (reduced ? sample_bricks(v)
+      {
+        const int nb = b.n_tiles * (reduced ? sample_bricks(v)
                                     : xd    ? (n / 2) * nxbh
                                     : hy    ? (n / 2) * nxb
-                                            : br));
+                                            : br);
+        int rows = 1;
+        for (int t = 0; t < b.n_tiles; ++t) rows = std::max(rows, sp.tiles[b.tile_off + t].nI);
+        PassArgs& pa = g.a[who.size() - 1];
+        pa.fwd_rows = (rows + fwd_chunks(nb, rows) - 1) / fwd_chunks(nb, rows);
+        pa.fwd_chunks = (rows + pa.fwd_rows - 1) / pa.fwd_rows;
+        nb_fwd.push_back(nb * pa.fwd_chunks);
+      }
+      // a half-length forward z transform reads the orbitals on even z only,
+      // half-height input on even y only (and stores half the rows);
+      // half-width input stores half the columns (its orbital reads, every
+      // other point of a row, still move whole rows)
       // share of a kept plane's points that pass 1 stores
       const double pf = reduced ? (double)v->nf * v->nf / ((double)n * n) : yf * xf;
       by_fwd += orbs * nr * elem * (reduced ? ns : (half_z(v, sp.kz_max) ? 0.5 : 1.0) * yf) +

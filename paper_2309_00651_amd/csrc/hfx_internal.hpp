@@ -77,6 +77,9 @@ struct PassArgs {
   // N / 2: every column is kept).
   int kx_max;
   int ky_max;  // the same along y
+  // Pass 1: a tile pair's rows are dealt to fwd_chunks workgroups per brick,
+  // fwd_rows each (its rows write disjoint pair grids)
+  int fwd_rows, fwd_chunks;
 };
 
 // Zero block of band-limited plans (the pruned planes' loads read its first
