@@ -243,7 +243,7 @@ bool launch_apply_left_f32(const double* m, const float* src, double* dst, int n
 hipError_t prepare_apply_left();
 
 // SCDM pivot selection (scdm.hip)
-constexpr int kScdmParts = 2048;  // workgroups of the grid-wide passes
+constexpr int kScdmParts = 2048;  // most workgroups of a downdating step
 size_t scdm_scratch_bytes(long long nr);
 // piv[k] (k < n) = grid points chosen by column-pivoted QR of psi^T (n x nr);
 // scratch: scdm_scratch_bytes(nr); qm: n x n doubles (rows q_k)
