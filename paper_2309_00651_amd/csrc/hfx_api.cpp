@@ -1104,7 +1104,8 @@ hfx_status enq_ace_build(hfx_plan plan, SystemPlan& sp, const void* kpsi, const 
     // P = X W straight from the float64 K psi
     launch_apply_left(inv, reinterpret_cast<const double*>(kp), pp, n, sp.nr, tmp, st);
     bk.done(nn * npts * 16.0, 2.0 * nn * nn * npts);
-  } else if (launch_apply_left_f32(inv, reinterpret_cast<const float*>(kp), pp, n, sp.nr, st)) {
+  } else if (launch_apply_left_f32(inv, reinterpret_cast<const float*>(kp), pp, n, sp.nr, tmp,
+                                   st)) {
     // float32 K psi widened while staged
     bk.done(nn * npts * (elem + 8.0), 2.0 * nn * nn * npts);
   } else {
@@ -1520,16 +1521,11 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
   };
   if (hipGetDevice(&p->device) != hipSuccess)
     return cleanup(fail(HFX_EDEVICE, "no HIP device available"));
-  {
-    hipError_t e = prepare_apply_left();
-    if (e == hipSuccess) e = prepare_resample();
-    if (e != hipSuccess)
-      return cleanup(fail(HFX_EDEVICE, std::string("kernel set-up: ") + hipGetErrorString(e)));
-  }
   for (auto& sp : p->sys) {
     hfx_status s;
     if (sp.pv()->prepare) {
       hipError_t e = sp.pv()->prepare();
+      if (e == hipSuccess && sp.rvar) e = prepare_resample();
       if (e != hipSuccess)
         return cleanup(fail(HFX_EDEVICE, std::string("kernel set-up: ") + hipGetErrorString(e)));
     }

@@ -239,8 +239,7 @@ void launch_apply_left(const double* m, const double* src, double* dst, int n, l
                        double* tmp, hipStream_t st);
 // dst <- m widen(src), float32 src (n <= 512; false otherwise, nothing launched)
 bool launch_apply_left_f32(const double* m, const float* src, double* dst, int n, long long nr,
-                           hipStream_t st);
-hipError_t prepare_apply_left();
+                           double* tmp, hipStream_t st);
 
 // SCDM pivot selection (scdm.hip)
 constexpr int kScdmParts = 2048;  // most workgroups of a downdating step

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "hfx_internal.hpp"
 
@@ -248,135 +249,129 @@ hipError_t launch_inverse_sqrt(double* s, int n, double* work, int max_iter, hip
   return hipGetLastError();
 }
 
-// psi <- m psi in place, one block of CB grid points per workgroup: the
-// block (all n orbitals) is staged in LDS, so the workgroup may overwrite it
-// in HBM; m (n x n, a few hundred KB) is read by every workgroup and stays in
-// L2.  4 wavefronts share the output rows, BM 16-row MFMA blocks each.  The
-// contraction index k is permuted per lane (lane group g = l / 16 takes
-// k = k0 + 4 g + j for MFMA step j) so that each lane reads four consecutive
-// m values per row with one vector load; the block rows are read from LDS in
-// the same order.
-// S: element type of the source (float32 sources are widened while staged).
-template <int BM, int CB, typename S>
-__global__ void __launch_bounds__(256) k_apply_left(const double* __restrict__ m, int n,
-                                                    const S* src, double* dst, long long nr) {
-  constexpr int BN = CB / 16;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double* blk = reinterpret_cast<double*>(smem_raw);  // [k][CB + 2], k < npad
-  constexpr int LD = CB + 2;                            // 16-byte aligned rows
-  const int npad = (n + 15) / 16 * 16;
-  const long long c0 = (long long)blockIdx.x * CB;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, g = lane >> 4;
-  // stage the block (rows beyond n and columns beyond nr as zeros), two
-  // doubles per load: nr is even (n^3, n even) and c0 a multiple of CB
-  constexpr int PR = CB / 2;  // pairs per row
-  constexpr int U = 8;        // loads in flight per thread
-  const int total = npad * PR;
-  for (int e0 = 0; e0 < total; e0 += 256 * U) {
-    double2 v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = e0 + tid + 256 * u;
-      const int k = e / PR, cc = 2 * (e - k * PR);
-      v[u] = double2{0.0, 0.0};
-      if (e < total && k < n && c0 + cc + 1 < nr) {
-        if constexpr (sizeof(S) == 8) {
-          v[u] = *reinterpret_cast<const double2*>(src + (long long)k * nr + c0 + cc);
-        } else {
-          const float2 f = *reinterpret_cast<const float2*>(src + (long long)k * nr + c0 + cc);
-          v[u] = double2{(double)f.x, (double)f.y};
-        }
-      } else if (e < total && k < n && c0 + cc < nr) {
-        v[u].x = (double)src[(long long)k * nr + c0 + cc];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = e0 + tid + 256 * u;
-      const int k = e / PR, cc = 2 * (e - k * PR);
-      if (e < total) *reinterpret_cast<double2*>(blk + k * LD + cc) = v[u];
-    }
-  }
+// dst = m src for n <= 512 rows, dst == src allowed.
+//
+// A wavefront owns RB 16-row blocks of the result and two 16-column tiles; the
+// RW wavefronts that share the columns cover the rows, so a workgroup reads all
+// it needs of its columns before its barrier and may then overwrite them.
+// Nothing is staged in LDS: src rows are the B operand as they lie (128-byte
+// segments), and m comes in fragment order from L2 (k_fragments), one
+// contiguous 512-byte load per 16 x 4 block that feeds both column tiles.  The
+// operands of two steps are in flight.  Bound by the float64 matrix rate: 116
+// GFLOP at 256 orbitals on 96^3.  (Columns staged in LDS, 64 KB per workgroup,
+// and m read from its rows with branches around the edges took 3.25 ms there:
+// a staging phase that nothing hides, and waits at every branch.)
+//
+// Fragment ((4-column step s, 16-row block p), lane l) of m: m[16 p + l % 16]
+// [4 s + l / 16], zero beyond n.
+__global__ void __launch_bounds__(256) k_fragments(const double* __restrict__ m, int n, int blocks,
+                                                   int total, double* __restrict__ frag) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= total) return;
+  const int l = e & 63, p = (e >> 6) % blocks, s = (e >> 6) / blocks;
+  const int row = 16 * p + (l & 15), col = 4 * s + (l >> 4);
+  frag[e] = row < n && col < n ? m[(long long)row * n + col] : 0.0;
+}
+
+template <int RB, typename S>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_apply_left(const double* __restrict__ frag, int n, int blocks, int rw, const S* src, double* dst,
+             long long nr) {
+  constexpr int NC = 2, D = 2;
   typedef double f64x4 __attribute__((ext_vector_type(4)));
-  f64x4 acc[BM][BN];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int cw = (int)(blockDim.x >> 6) / rw;  // column groups of the workgroup
+  const int p0 = (wave % rw) * RB;             // first row block (blocks is a multiple of RB)
+  const long long c0 = ((long long)blockIdx.x * cw + wave / rw) * 16 * NC + lr;
+  const S* col[NC];
 #pragma unroll
-  for (int p = 0; p < BM; ++p)
+  for (int q = 0; q < NC; ++q) col[q] = src + (c0 + 16 * q < nr ? c0 + 16 * q : 0);
+  const double* f = frag + (long long)p0 * 64 + lane;
+  const int steps = (n + 3) / 4;
+  double r[D][RB];
+  S x[D][NC];
+  auto load = [&](int k, int s) {
+    const int at = s < steps ? s : steps - 1;
+    const int row = 4 * at + lk < n ? 4 * at + lk : n - 1;
 #pragma unroll
-    for (int q = 0; q < BN; ++q) acc[p][q] = f64x4{0.0, 0.0, 0.0, 0.0};
-  // m fragments of rows (wave + 4 p) * 16 + lr, k = k0 + 4 g + (0..3)
-  auto load_m = [&](int k0, double (*av)[4]) {
-    const int kb = k0 + 4 * g;
+    for (int q = 0; q < NC; ++q) x[k][q] = col[q][(long long)row * nr];
 #pragma unroll
-    for (int p = 0; p < BM; ++p) {
-      const int row = (wave + 4 * p) * 16 + lr;
-      if (row < n && kb + 4 <= n && (n & 1) == 0) {  // 16-byte aligned rows
-        const double2* src = reinterpret_cast<const double2*>(m + (long long)row * n + kb);
-        const double2 x = src[0], y = src[1];
-        av[p][0] = x.x;
-        av[p][1] = x.y;
-        av[p][2] = y.x;
-        av[p][3] = y.y;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          av[p][j] = (row < n && kb + j < n) ? m[(long long)row * n + kb + j] : 0.0;
-      }
-    }
+    for (int p = 0; p < RB; ++p) r[k][p] = f[((long long)at * blocks + p) * 64];
+    asm volatile("" ::: "memory");  // or the loads sink to their use in a later step
   };
-  double av[BM][4], an[BM][4];
-  load_m(0, av);
-  __syncthreads();
-  for (int k0 = 0; k0 < npad; k0 += 16) {
-    if (k0 + 16 < npad) load_m(k0 + 16, an);  // next fragments in flight
-    const int kb = k0 + 4 * g;
+  f64x4 acc[RB][NC];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      double bv[BN];
+  for (int p = 0; p < RB; ++p)
 #pragma unroll
-      for (int q = 0; q < BN; ++q) bv[q] = blk[(kb + j) * LD + 16 * q + lr];
+    for (int q = 0; q < NC; ++q) acc[p][q] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int p = 0; p < BM; ++p)
+  for (int k = 0; k < D; ++k) load(k, k);
+  for (int s = 0; s < steps; s += D)
 #pragma unroll
-        for (int q = 0; q < BN; ++q)
-          acc[p][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[p][j], bv[q], acc[p][q], 0, 0, 0);
+    for (int k = 0; k < D; ++k) {
+      if (s + k < steps) {
+        // rows beyond n (last step): zeros, not the clamped row times zero
+        const bool in = 4 * (s + k) + lk < n;
+#pragma unroll
+        for (int p = 0; p < RB; ++p)
+#pragma unroll
+          for (int q = 0; q < NC; ++q)
+            acc[p][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[k][p], in ? (double)x[k][q] : 0.0,
+                                                             acc[p][q], 0, 0, 0);
+      }
+      load(k, s + k + D);
     }
-#pragma unroll
-    for (int p = 0; p < BM; ++p)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) av[p][j] = an[p][j];
-  }
+  __syncthreads();  // every wavefront has read the workgroup's columns
   // result i of lane l: row (l / 16) + 4 i of the block, column l % 16
 #pragma unroll
-  for (int p = 0; p < BM; ++p)
+  for (int p = 0; p < RB; ++p)
 #pragma unroll
-    for (int q = 0; q < BN; ++q)
+    for (int q = 0; q < NC; ++q)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row = (wave + 4 * p) * 16 + g + 4 * i;
-        const long long col = c0 + 16 * q + lr;
-        if (row < n && col < nr) dst[(long long)row * nr + col] = acc[p][q][i];
+        const int row = 16 * (p0 + p) + lk + 4 * i;
+        if (row < n && c0 + 16 * q < nr) dst[(long long)row * nr + c0 + 16 * q] = acc[p][q][i];
       }
 }
 
-// dst <- m src (n x n times n x nr; dst == src allowed: each workgroup reads
-// its whole column block before writing it).  n <= 512: one pass
+// Launches k_apply_left for n <= 512; tmp holds the fragments of m
+// (2 n + 80 values per row at most: n x min(nr, 32768) doubles are there).
+template <typename S>
+static void apply_left(const double* m, const S* src, double* dst, int n, long long nr, double* tmp,
+                       hipStream_t st) {
+  const int nb = (n + 15) / 16;
+  const int rw = (nb + 7) / 8;          // row wavefronts, up to 8 blocks each
+  const int rb = (nb + rw - 1) / rw;    // blocks per wavefront
+  const int blocks = rw * rb, total = (n + 3) / 4 * blocks * 64;
+  hipLaunchKernelGGL(k_fragments, dim3((total + 255) / 256), dim3(256), 0, st, m, n, blocks, total,
+                     tmp);
+  const int cw = 4 / rw;
+  const long long per = (long long)cw * 32;
+  const dim3 grid((unsigned)((nr + per - 1) / per)), block(64 * rw * cw);
+  auto go = [&](auto rbc) {
+    hipLaunchKernelGGL((k_apply_left<decltype(rbc)::value, S>), grid, block, 0, st, tmp, n, blocks,
+                       rw, src, dst, nr);
+  };
+  switch (rb) {
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    case 5: go(std::integral_constant<int, 5>{}); break;
+    case 6: go(std::integral_constant<int, 6>{}); break;
+    case 7: go(std::integral_constant<int, 7>{}); break;
+    default: go(std::integral_constant<int, 8>{});
+  }
+}
+
+// dst <- m src (n x n times n x nr; dst == src allowed).  n <= 512: one pass
 // (k_apply_left); larger n: column chunks through tmp (n x 32768 doubles)
 // and a copy to dst.
 void launch_apply_left(const double* m, const double* src, double* dst, int n, long long nr,
                        double* tmp, hipStream_t st) {
-  if (n <= 256) {
-    constexpr int CB = 32;
-    const size_t lds = (size_t)((n + 15) / 16 * 16) * (CB + 2) * 8;
-    hipLaunchKernelGGL((k_apply_left<4, CB, double>), dim3((unsigned)((nr + CB - 1) / CB)), dim3(256),
-                       lds, st, m, n, src, dst, nr);
-    return;
-  }
   if (n <= 512) {
-    constexpr int CB = 16;
-    const size_t lds = (size_t)((n + 15) / 16 * 16) * (CB + 2) * 8;
-    hipLaunchKernelGGL((k_apply_left<8, CB, double>), dim3((unsigned)((nr + CB - 1) / CB)), dim3(256),
-                       lds, st, m, n, src, dst, nr);
+    apply_left(m, src, dst, n, nr, tmp, st);
     return;
   }
   const long long cc = 32768;
@@ -392,36 +387,10 @@ void launch_apply_left(const double* m, const double* src, double* dst, int n, l
 // dst <- m widen(src) for a float32 source (n <= 512, dst distinct from
 // src); returns false for larger n, where the caller widens first.
 bool launch_apply_left_f32(const double* m, const float* src, double* dst, int n, long long nr,
-                           hipStream_t st) {
-  if (n <= 256) {
-    constexpr int CB = 32;
-    const size_t lds = (size_t)((n + 15) / 16 * 16) * (CB + 2) * 8;
-    hipLaunchKernelGGL((k_apply_left<4, CB, float>), dim3((unsigned)((nr + CB - 1) / CB)),
-                       dim3(256), lds, st, m, n, src, dst, nr);
-    return true;
-  }
-  if (n <= 512) {
-    constexpr int CB = 16;
-    const size_t lds = (size_t)((n + 15) / 16 * 16) * (CB + 2) * 8;
-    hipLaunchKernelGGL((k_apply_left<8, CB, float>), dim3((unsigned)((nr + CB - 1) / CB)),
-                       dim3(256), lds, st, m, n, src, dst, nr);
-    return true;
-  }
-  return false;
-}
-
-// Raise the dynamic-LDS limit of the in-place kernels (once per process).
-hipError_t prepare_apply_left() {
-  const void* k[4] = {reinterpret_cast<const void*>(&k_apply_left<4, 32, double>),
-                      reinterpret_cast<const void*>(&k_apply_left<8, 16, double>),
-                      reinterpret_cast<const void*>(&k_apply_left<4, 32, float>),
-                      reinterpret_cast<const void*>(&k_apply_left<8, 16, float>)};
-  const int bytes[4] = {256 * 34 * 8, 512 * 18 * 8, 256 * 34 * 8, 512 * 18 * 8};
-  for (int i = 0; i < 4; ++i) {
-    hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+                           double* tmp, hipStream_t st) {
+  if (n > 512) return false;
+  apply_left(m, src, dst, n, nr, tmp, st);
+  return true;
 }
 
 }  // namespace hfx
