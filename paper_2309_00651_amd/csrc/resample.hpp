@@ -37,21 +37,28 @@ constexpr int kMaxLen = 128;
 size_t resample_entries(int a, int b) { return (size_t)(a / 4) * ((b + 15) / 16) * 64; }
 
 void resample_matrix(int a, int b, int kmax, double* out) {
-  const int ab = a * b;
-  const int rb = (b + 15) / 16;
-  std::vector<long double> c(ab);  // entries rounded to float64 once
-  for (int t = 0; t < ab; ++t) c[t] = std::cos(2.0L * 3.14159265358979323846264338327950288L * t / ab);
+  // R depends on d = (i/b - j/a) ab mod ab alone; the sum over k in closed form,
+  // sin((2 kmax + 1) pi d / ab) / sin(pi d / ab), its angles reduced exactly
+  const int ab = a * b, rb = (b + 15) / 16;
+  const long double pi = 3.14159265358979323846264338327950288L;
+  std::vector<double> val(ab, 0.0);
+  std::vector<char> known(ab, 0);
   for (int s = 0; s < a / 4; ++s)
     for (int p = 0; p < rb; ++p)
       for (int l = 0; l < 64; ++l) {
         const int i = 16 * p + l % 16, j = 4 * s + l / 16;
-        long double v = 0.0L;
+        double v = 0.0;
         if (i < b) {
-          const int d = ((i * a - j * b) % ab + ab) % ab;  // (i/b - j/a) ab
-          for (int k = kmax; k >= 1; --k) v += c[(int)((long long)k * d % ab)];
-          v = (1.0L + 2.0L * v) / a;
+          const int d = ((i * a - j * b) % ab + ab) % ab;
+          if (!known[d]) {
+            const long long m = (2LL * kmax + 1) * d % (2LL * ab);
+            val[d] = d == 0 ? (double)((2 * kmax + 1) / (long double)a)
+                            : (double)(std::sin(pi * m / ab) / (std::sin(pi * d / ab) * a));
+            known[d] = 1;
+          }
+          v = val[d];
         }
-        out[((size_t)s * rb + p) * 64 + l] = (double)v;
+        out[((size_t)s * rb + p) * 64 + l] = v;
       }
 }
 
