@@ -350,10 +350,7 @@ __global__ void __launch_bounds__(NT) k_pair_fwd(PassGroup grp) {
         // pairs not evaluated (screened, or below the diagonal) transform as
         // zeros, so they add no rounding to the pair sharing their grid; the
         // half-length transform takes doubled products
-        on[q] = pair_live<TT, SCR>(td, ia, b0 + q)
-                    ? T(ZS * YS * XS) *
-                          (td.diag && b0 + q + td.joff == ia ? (T)a.diag_scale : T(1))
-                    : T(0);
+        on[q] = pair_live<TT, SCR>(td, ia, b0 + q) ? T(ZS * YS * XS) : T(0);
       }
 #pragma unroll
       for (int k = 0; k < PT; ++k)
@@ -1322,159 +1319,6 @@ __global__ void __launch_bounds__(NT) k_cols_conv(PassGroup grp) {
 }
 
 // ---------------------------------------------------------------------------
-// Energy without potentials.  By Parseval's theorem the pair energies of a
-// grid need no inverse transform: with c = rho_1 + i rho_2 and v even,
-// sum_G v(G) |c(G)|^2 = sum_r (rho_1 v_1 + rho_2 v_2) (the cross terms cancel
-// between G and -G), so the forward half of the plane pass ends in a sum.  An
-// energy call then reads each pair grid once after pass 1, where the
-// potentials' route writes it, reads it and transforms it back along x, y and
-// z.  Pass 1 scales the densities of diagonal pairs by sqrt(1/2)
-// (PassArgs::diag_scale): every pair then has weight 2.
-//
-// A launch has one workgroup per brick of its tile pairs (one partial sum each,
-// as pass 3 has); workgroup l takes the planes l, l + workgroups, ... and loads
-// the rows of its next plane while it transforms the current one.
-// VN, VNZ: the pair grids' (and the table's) points per axis; N < VN: planes of
-// N x N samples (reduced pair grids), whose frequencies beyond the band are
-// left out.
-template <typename T, int N, int NT, class SXF, class SYF, int VN = N, int VNZ = N>
-__global__ void __launch_bounds__(NT) k_plane_energy(PassGroup grp) {
-  int sys_ = 0;
-  const int lg = grp.locate(xcd_remap(blockIdx.x, gridDim.x), sys_);
-  const PassArgs& a = grp.a[sys_];
-  const int wgs = grp.start[sys_ + 1] - grp.start[sys_];
-  constexpr int P = N + 1;
-  using GX = Geom<T, N, N, NT, false, 1, P>;
-  using GY = Geom<T, N, N, NT, true, P, 1>;
-  using EX = FFT<GX, false, SXF>;
-  using EY = FFT<GY, false, SYF>;
-  using FX = FirstStage<GX, SXF>;
-  using LX = LastStage<GX, SXF>;
-  using LY = LastStage<GY, SYF>;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  cpx<T>* plane = reinterpret_cast<cpx<T>*>(smem_raw);
-  __shared__ TwEntry<T> twx[tw_slots<T, SXF>()], twy[tw_slots<T, SYF>()];
-  const int tid = threadIdx.x;
-  // reduced grids: the forward x and y schedule is the plan's zh
-  stage_twiddles<T, SXF, NT>(twx, VN == N ? a.tw_xf : a.tw_zh, tid);
-  stage_twiddles<T, SYF, NT>(twy, VN == N ? a.tw_yf : a.tw_zh, tid);
-  const int total = a.n_active * kz_planes(VNZ, a.kz_max);
-  const cpx<T>* __restrict__ gbase = static_cast<const cpx<T>*>(a.grids);
-  auto kz_at = [&](int L) { return kz_of_plane(L / a.n_active, VNZ, a.kz_max); };
-  auto load_rows = [&](int L, cpx<T>* v, int t) {
-    const int c = L / a.n_active;
-    const cpx<T>* base = gbase + (long long)a.active[L - c * a.n_active] * ((long long)VNZ * VN * VN) +
-                         (long long)kz_at(L) * VN * VN;
-#pragma unroll
-    for (int i = 0; i < FX::PER; ++i) {
-      if (!FX::valid(t, i)) continue;
-      int m, j;
-      FX::mj(t, i, m, j);
-#pragma unroll
-      for (int r = 0; r < SchedInfo<SXF>::first; ++r)
-        v[i * SchedInfo<SXF>::first + r] = base[m * N + FX::in_pos(j, r)];
-    }
-  };
-  double eacc = 0.0;
-  cpx<T> v[FX::VALS];
-  int L = lg;
-  if (L < total) load_rows(L, v, tid);
-  __syncthreads();  // twiddles
-  for (; L < total; L += wgs) {
-    // opaque once per plane, so that the LDS and HBM offsets are recomputed
-    // instead of kept live across the loop
-    int t = tid;
-    asm volatile("" : "+v"(t));
-    {
-      cpx<T> o[LX::VALS];
-      EX::reg2reg(v, plane, twx, t, o);
-      if (L + wgs < total) load_rows(L + wgs, v, t);
-      EX::store_last(o, plane, t);
-    }
-    __syncthreads();
-    cpx<T> y[LY::VALS];
-    EY::lds2reg(plane, twy, t, y);  // ends with a barrier after its last LDS read
-    const T* __restrict__ vt = static_cast<const T*>(a.vtab) + (long long)kz_at(L) * VN * VN;
-#pragma unroll
-    for (int i = 0; i < LY::PER; ++i) {
-      if (!LY::valid(t, i)) continue;
-      int m, j;
-      LY::mj(t, i, m, j);
-      const int kx = VN == N || 2 * m < N ? m : m + VN - N;
-#pragma unroll
-      for (int r = 0; r < SchedInfo<SYF>::last; ++r) {
-        const int k = LY::in_pos(j, r);
-        const int ky = VN == N || 2 * k < N ? k : k + VN - N;
-        if (VN != N && !(kz_kept(m, N, a.kx_max) && kz_kept(k, N, a.ky_max))) continue;
-        const cpx<T> c = y[i * SchedInfo<SYF>::last + r];
-        eacc += (double)(vt[ky * VN + kx] * (c.re * c.re + c.im * c.im));
-      }
-    }
-  }
-  __syncthreads();
-  const double sum = block_sum<NT>(eacc, reinterpret_cast<double*>(plane));
-  if (tid == 0) a.partials[a.part_base + lg] = sum;
-}
-
-// The same after the x rows pass of split planes: y columns of W points each.
-template <typename T, int N, int W, int NT, class SYF>
-__global__ void __launch_bounds__(NT) k_cols_energy(PassGroup grp) {
-  int sys_ = 0;
-  const int lg = grp.locate(xcd_remap(blockIdx.x, gridDim.x), sys_);
-  const PassArgs& a = grp.a[sys_];
-  const int wgs = grp.start[sys_ + 1] - grp.start[sys_];
-  using G = Geom<T, N, W, NT, true, W, 1>;
-  using E = FFT<G, false, SYF>;
-  using F = FirstStage<G, SYF>;
-  using L = LastStage<G, SYF>;
-  constexpr int NXB = (N + W - 1) / W;
-  constexpr long long NR = (long long)N * N * N;
-  __shared__ cpx<T> lds[N * W];
-  __shared__ TwEntry<T> tw[tw_slots<T, SYF>()];
-  static_assert(sizeof(cpx<T>) * N * W >= sizeof(double) * pow2_at_least<NT>(), "reduction space");
-  const int tid = threadIdx.x;
-  stage_twiddles<T, SYF, NT>(tw, a.tw_yf, tid);  // visible after the first barrier
-  const int per_grid = kz_planes(N, a.kz_max) * NXB;  // kept planes x column blocks
-  const int total = a.n_active * per_grid;
-  double eacc = 0.0;
-  for (int q = lg; q < total; q += wgs) {
-    const int ai = q / per_grid, rem = q - ai * per_grid;
-    const int zc = rem / NXB, x0 = (rem - zc * NXB) * W;
-    const int z = kz_of_plane(zc, N, a.kz_max);
-    const cpx<T>* __restrict__ base = static_cast<const cpx<T>*>(a.grids) +
-                                      (long long)a.active[ai] * NR + (long long)z * N * N;
-    const T* __restrict__ vt = static_cast<const T*>(a.vtab) + (long long)z * N * N;
-    cpx<T> v[F::VALS];
-#pragma unroll
-    for (int i = 0; i < F::PER; ++i) {
-      int m = 0, j = 0;
-      F::mj(tid, i, m, j);
-      const bool ok = F::valid(tid, i) && x0 + m < N;
-#pragma unroll
-      for (int r = 0; r < SchedInfo<SYF>::first; ++r)
-        v[i * SchedInfo<SYF>::first + r] =
-            ok ? base[F::in_pos(j, r) * N + x0 + m] : cpx<T>{T(0), T(0)};
-    }
-    cpx<T> o[L::VALS];
-    E::reg2reg(v, lds, tw, tid, o);  // ends with a barrier after its last LDS read
-#pragma unroll
-    for (int i = 0; i < L::PER; ++i) {
-      int m = 0, j = 0;
-      L::mj(tid, i, m, j);
-      if (!(L::valid(tid, i) && x0 + m < N)) continue;
-#pragma unroll
-      for (int r = 0; r < SchedInfo<SYF>::last; ++r) {
-        const cpx<T> c = o[i * SchedInfo<SYF>::last + r];
-        eacc += (double)(vt[L::in_pos(j, r) * N + x0 + m] * (c.re * c.re + c.im * c.im));
-      }
-    }
-  }
-  __syncthreads();
-  const double sum = block_sum<NT>(eacc, reinterpret_cast<double*>(lds));
-  if (tid == 0) a.partials[a.part_base + lg] = sum;
-}
-
-// ---------------------------------------------------------------------------
 // Registry glue: one compiled pipeline configuration.
 
 // Threads of the pair_fwd (FWD) and inv_acc passes.  float32: 256 for the
@@ -1673,21 +1517,7 @@ struct FusedPipeline {
   }
   static void inv_acc(const PassGroup& g, int nb, hipStream_t s) { inv_pass<true>(g, nb, s); }
   static void inv_energy(const PassGroup& g, int nb, hipStream_t s) { inv_pass<false>(g, nb, s); }
-  // float64 energies by Parseval (float32 keeps the potentials' route: its
-  // result would move by a few 1e-9 of E_x, the bias of the inverse transforms)
-  static constexpr bool EOK = sizeof(T) == 8 && PM == 1 && !SW;
-  static void energy(const PassGroup& g, int nb, hipStream_t s) {
-    if constexpr (EOK)
-      hipLaunchKernelGGL((k_plane_energy<T, N, NTQ, SXF, SYF, N, NZ>), dim3(nb), dim3(NTQ), lds, s,
-                         g);
-  }
   static hipError_t prepare() {
-    if constexpr (EOK) {
-      const hipError_t e = hipFuncSetAttribute(
-          reinterpret_cast<const void*>(&k_plane_energy<T, N, NTQ, SXF, SYF, N, NZ>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
     if constexpr (PM == 2)
       return hipFuncSetAttribute(
           reinterpret_cast<const void*>(&k_plane_h2<T, N, NTQ, SXF, SXI, SYF, SYI, NZ>),
@@ -1745,7 +1575,6 @@ struct FusedPipeline {
     v.plane = &plane;
     v.inv_acc = &inv_acc;
     v.inv_energy = &inv_energy;
-    v.energy = EOK ? &energy : nullptr;
     v.prepare = &prepare;
     return v;
   }
@@ -1807,25 +1636,7 @@ struct ReducedPipeline {
   }
   static void inv_acc(const PassGroup& g, int nb, hipStream_t s) { inv_pass<true>(g, nb, s); }
   static void inv_energy(const PassGroup& g, int nb, hipStream_t s) { inv_pass<false>(g, nb, s); }
-  // float64 energies by Parseval, on the sampling points alone
-  static constexpr bool EOK = sizeof(T) == 8;
-  static constexpr int NTE = NF * 8 <= 512 ? NF * 8 : 512;
-  static constexpr size_t lds_energy =
-      (size_t)NF * (NF + 1) * sizeof(cpx<T>) > sizeof(double) * pow2_at_least<NTE>()
-          ? (size_t)NF * (NF + 1) * sizeof(cpx<T>)
-          : sizeof(double) * pow2_at_least<NTE>();
-  static void energy(const PassGroup& g, int nb, hipStream_t s) {
-    if constexpr (EOK)
-      hipLaunchKernelGGL((k_plane_energy<T, NF, NTE, SXF, SXF, NI, NIZ>), dim3(nb), dim3(NTE),
-                         lds_energy, s, g);
-  }
   static hipError_t prepare() {
-    if constexpr (EOK) {
-      const hipError_t e = hipFuncSetAttribute(
-          reinterpret_cast<const void*>(&k_plane_energy<T, NF, NTE, SXF, SXF, NI, NIZ>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_energy);
-      if (e != hipSuccess) return e;
-    }
     return hipFuncSetAttribute(reinterpret_cast<const void*>(plane_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   }
@@ -1855,7 +1666,6 @@ struct ReducedPipeline {
     v.plane = &plane;
     v.inv_acc = &inv_acc;
     v.inv_energy = &inv_energy;
-    v.energy = EOK ? &energy : nullptr;
     v.prepare = &prepare;
     return v;
   }
@@ -1883,9 +1693,6 @@ struct SplitPipeline {
   }
   static void cols_conv(const PassGroup& g, int nb, hipStream_t s) {
     hipLaunchKernelGGL((k_cols_conv<T, N, W, NTC, SYF, SYI>), dim3(nb), dim3(NTC), 0, s, g);
-  }
-  static void energy(const PassGroup& g, int nb, hipStream_t s) {
-    hipLaunchKernelGGL((k_cols_energy<T, N, W, NTC, SYF>), dim3(nb), dim3(NTC), 0, s, g);
   }
   // screened (perm) and band-limited (kz_max < N / 2: pruned loads skipped)
   // plans take their own instantiations
@@ -1946,7 +1753,6 @@ struct SplitPipeline {
     v.rows_inv = &rows_inv;
     v.inv_acc = &inv_acc;
     v.inv_energy = &inv_energy;
-    v.energy = &energy;
     v.prepare = &prepare;
     return v;
   }

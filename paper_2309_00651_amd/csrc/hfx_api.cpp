@@ -624,7 +624,6 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
                         hipStream_t st, bool acc) {
   const Variant* v = calls[0].sp->pv();
   const bool reduced = calls[0].sp->rvar != nullptr;
-  const bool parseval = !acc && v->energy;  // energies without potentials
   const size_t elem = plan->prec == HFX_FP64 ? 8 : 4;
   const int nc = (int)calls.size();
   std::vector<PassArgs> args(nc);
@@ -691,9 +690,8 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     const void* psi_w = psi;
     const double orb_pts = (double)sp.sys.n_orb * (double)sp.nr;
     if (reduced) {
-      // the orbitals at the sampling points and, for the potentials' passes, on
-      // the pair grid (the pair-grid buffer is free until pass 1 and serves as
-      // scratch)
+      // the orbitals at the sampling points and on the pair grid (the pair-grid
+      // buffer is free until pass 1 and serves as scratch)
       const int n = sp.sys.n[0], nz = sp.sys.n[2], no = sp.sys.n_orb;
       double* samp = reinterpret_cast<double*>(ws + sp.off_samp);
       float* samp32 =
@@ -701,9 +699,7 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       Bracket br(plan, HFX_PASS_STAGE, st);
       launch_decimate(psi, no, n, nz, samp, samp32, st);
       const double *rx = static_cast<double*>(sp.d_rs[0]), *rz = static_cast<double*>(sp.d_rs[1]);
-      if (parseval) {
-        // pass 1 needs the sampling points alone
-      } else if (samp32)
+      if (samp32)
         launch_resample(psi, reinterpret_cast<float*>(ws + sp.off_psig), no, n, nz, v->n, v->nz,
                         rx, rz, ws + sp.off_grids, sp.grid_bytes, st);
       else
@@ -767,7 +763,6 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     a.kx_max = sp.kx_max;
     a.ky_max = sp.ky_max;
     a.zero = sp.d_zero;
-    a.diag_scale = parseval ? std::sqrt(0.5) : 1.0;
     max_batches = std::max(max_batches, sp.batches.size());
   }
   const int br = bricks_per_tile(v);
@@ -795,7 +790,6 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     // algorithmic bytes and flops of each pass over them
     PassGroup g{};
     std::vector<int> who;
-    double by_en = 0;  // the pair grids once (energy pass)
     double by_fwd = 0, fl_fwd = 0, by_pl = 0, fl_pl = 0, by_row = 0, fl_row = 0, by_col = 0,
            fl_col = 0, by_inv = 0, fl_inv = 0;
     std::vector<int> nb_fwd, nb_pl, nb_row, nb_col, nb_inv;
@@ -874,7 +868,6 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       fl_fwd += grids * fft_z * (reduced ? ns : yf * xf);
       nb_pl.push_back(b.n_active * kp);
       by_pl += grids * nr * ce * (1.0 + pf) * kzf;
-      by_en += grids * nr * ce * pf * kzf;
       fl_pl += grids * fft_axis * 4.0 * kzf;
       nb_row.push_back(b.n_active * ((kp * n + v->rows_per_wg - 1) / std::max(v->rows_per_wg, 1)));
       by_row += grids * nr * ce * 2.0 * kzf;
@@ -900,14 +893,6 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       bk.done(bytes, flops);
     };
     launch(v->pair_fwd, nb_fwd, HFX_PASS_PAIR_FWD, by_fwd, fl_fwd);
-    if (parseval) {
-      // one workgroup and partial sum per tile pair and brick, as pass 3
-      if (v->plane_mode != 0) launch(v->rows_fwd, nb_row, HFX_PASS_ROWS_FWD, by_row, fl_row);
-      launch(v->energy, nb_inv, HFX_PASS_PLANE, v->plane_mode != 0 ? 0.5 * by_col : by_en,
-             v->plane_mode != 0 ? 0.5 * fl_col : 0.5 * fl_pl);
-      if (two) HIP_TRY(hipEventRecord(sp0.ev_acc[q], bs));
-      continue;
-    }
     if (v->plane_mode == 0) {
       launch(v->plane, nb_pl, HFX_PASS_PLANE, by_pl, fl_pl);
     } else {
@@ -953,11 +938,7 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     const double om = sp.dv * (double)sp.nr;
     // the G = 0 energy of the means is not pair work: added by group 0 only
     const bool dc = sp.shard == 0;
-    // by Parseval: every pair has weight 2 / 2, and the sums run over the points
-    // the forward transforms take
-    launch_energy_reduce(args[c].partials, sp.n_partials,
-                         parseval ? -om / (double)sp.sample_points()
-                                  : -0.5 * om / (double)sp.grid_points(),
+    launch_energy_reduce(args[c].partials, sp.n_partials, -0.5 * om / (double)sp.grid_points(),
                          dc ? args[c].mean : nullptr, sp.sys.n_orb,
                          dc ? -0.5 * om * sp.v0 : 0.0, calls[c].ex, st);
     bk.done((double)sp.n_partials * 8.0, 0.0);

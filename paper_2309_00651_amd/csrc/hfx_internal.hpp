@@ -80,9 +80,6 @@ struct PassArgs {
   // Pass 1: a tile pair's rows are dealt to fwd_chunks workgroups per brick,
   // fwd_rows each (its rows write disjoint pair grids)
   int fwd_rows, fwd_chunks;
-  // Factor of the diagonal pairs' densities: 1, or sqrt(1/2) in front of an
-  // energy pass (all pairs then count twice)
-  double diag_scale;
 };
 
 // Zero block of band-limited plans (the pruned planes' loads read its first
@@ -160,9 +157,6 @@ struct Variant {
   launch_fn rows_inv;          // plane_mode 1: inverse x FFT on rows
   launch_fn inv_acc;           // inverse z FFT + energy + K psi accumulation
   launch_fn inv_energy;        // inverse z FFT + energy only
-  // x (plane_mode 0) and y forward + energy by Parseval, in place of all that
-  // follows pass 1 (plane_mode 1: rows_fwd); null: not compiled
-  launch_fn energy;
   hipError_t (*prepare)();     // raise dynamic-LDS limits of the kernels
 };
 
