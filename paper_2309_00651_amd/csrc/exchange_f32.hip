@@ -10,20 +10,28 @@ namespace {
 // occupancy that hides the LDS and HBM latencies.
 using P24 = FusedPipeline<float, 24, 16, 8, Sched<4, 6>, Sched<6, 4>, 144, Sched<4, 6>,
                           Sched<6, 4>, Sched<4, 6>, Sched<6, 4>>;
-using P64 = FusedPipeline<float, 64, 16, 8, Sched<8, 8>, Sched<8, 8>, 256, Sched<8, 8>,
-                          Sched<8, 8>, Sched<8, 8>, Sched<8, 8>>;
+// 64 to 80 take the flat loads of the large grids in their accumulation (see
+// below; the registers they free bring the prefetch forward), and 64 a plane
+// of 512 threads (us per K psi, before / after: 64 orbitals on 64^3 2648 /
+// 2572, 128 at 20 Ha on 72^3 15290 / 15211, on 80^3 20689 / 20494; 96^3 is
+// not faster with them).
+using P64 = FusedPipeline<float, 64, 16, 8, Sched<8, 8>, Sched<8, 8>, 512, Sched<8, 8>,
+                          Sched<8, 8>, Sched<8, 8>, Sched<8, 8>, false, 256, 512, true, true,
+                          false, false, 64, 1>;
 using P64q512 = FusedPipeline<float, 64, 16, 8, Sched<8, 8>, Sched<8, 8>, 512, Sched<8, 8>,
                               Sched<8, 8>, Sched<8, 8>, Sched<8, 8>>;
 using P64r = FusedPipeline<float, 64, 16, 8, Sched<8, 8>, Sched<8, 8>, 256, Sched<8, 8>,
                            Sched<8, 8>, Sched<8, 8>, Sched<8, 8>, false, 256, 512, false, false>;
 using P72 = FusedPipeline<float, 72, 16, 8, Sched<8, 9>, Sched<9, 8>, 576, Sched<8, 9>,
-                          Sched<9, 8>, Sched<8, 9>, Sched<9, 8>>;
+                          Sched<9, 8>, Sched<8, 9>, Sched<9, 8>, false, 256, 512, true, true,
+                          false, false, 72, 1>;
 using P72q216 = FusedPipeline<float, 72, 16, 8, Sched<8, 9>, Sched<9, 8>, 216, Sched<8, 9>,
                               Sched<9, 8>, Sched<8, 9>, Sched<9, 8>>;
 using P72r = FusedPipeline<float, 72, 16, 8, Sched<8, 9>, Sched<9, 8>, 576, Sched<8, 9>,
                            Sched<9, 8>, Sched<8, 9>, Sched<9, 8>, false, 256, 512, false, false>;
 using P80 = FusedPipeline<float, 80, 16, 8, Sched<8, 10>, Sched<10, 8>, 640, Sched<8, 10>,
-                          Sched<10, 8>, Sched<8, 10>, Sched<10, 8>>;
+                          Sched<10, 8>, Sched<8, 10>, Sched<10, 8>, false, 256, 512, true, true,
+                          false, false, 80, 1>;
 using P80q320 = FusedPipeline<float, 80, 16, 8, Sched<8, 10>, Sched<10, 8>, 320, Sched<8, 10>,
                               Sched<10, 8>, Sched<8, 10>, Sched<10, 8>>;
 using P80r = FusedPipeline<float, 80, 16, 8, Sched<8, 10>, Sched<10, 8>, 640, Sched<8, 10>,
@@ -109,29 +117,36 @@ using P128pp = FusedPipeline<float, 128, 16, 8, Sched<8, 16>, Sched<16, 8>, 1024
 using P24x48 = FusedPipeline<float, 24, 16, 8, Sched<4, 12>, Sched<12, 4>, 144, Sched<4, 6>,
                              Sched<6, 4>, Sched<4, 6>, Sched<6, 4>, false, 256, 512, true, true,
                              false, false, 48>;
-using P64x128 = FusedPipeline<float, 64, 16, 8, Sched<8, 16>, Sched<16, 8>, 256, Sched<8, 8>,
-                              Sched<8, 8>, Sched<8, 8>, Sched<8, 8>, false, 256, 1024, false, false,
-                              false, false, 128>;
+// 64^2 x 128: flat prefetching loads as at 128^3 and 512 plane threads (64
+// orbitals 5613 -> 5072 us, two channels of 21 and 18 1557 -> 1451)
+using P64x128 = FusedPipeline<float, 64, 16, 8, Sched<8, 16>, Sched<16, 8>, 512, Sched<8, 8>,
+                              Sched<8, 8>, Sched<8, 8>, Sched<8, 8>, false, 256, 1024, false, true,
+                              false, false, 128, 1>;
 // Reduced pair grids of band-limited plans on grids that oversample the pair
 // densities twofold.
 // ReducedPipeline<T, forward points, inverse points, W, tile, plane threads,
 //                 x inv, y inv, z inv, pair_fwd threads, inv_acc threads,
 //                 psi J block in LDS, prefetch, flat loads [, z points]>
-using R64 = ReducedPipeline<float, 32, 48, 16, 8, 384, Sched<6, 8>, Sched<6, 8>, Sched<6, 8>, 256,
-                            384, true, true>;
+// Threads by measurement, pass times in ms (64 orbitals on 64^3: plane 0.300
+// with 384 threads, 0.273 with 256, accumulation 0.595 with 384 and 6 x 8, 0.559
+// with 256 and 8 x 6; 128 on 96^3: plane 3.52 with 576, 3.22 with 384; 101 on
+// 108^3: plane 3.19 with 640, 2.83 with 480).  Four grids per accumulation
+// transform and flat loads were slower on all of them.
+using R64 = ReducedPipeline<float, 32, 48, 16, 8, 256, Sched<6, 8>, Sched<6, 8>, Sched<8, 6>, 256,
+                            256, true, true>;
 using R72 = ReducedPipeline<float, 36, 60, 16, 8, 480, Sched<6, 10>, Sched<6, 10>, Sched<6, 10>,
                             256, 480, true, true>;
 using R80 = ReducedPipeline<float, 40, 60, 16, 8, 480, Sched<6, 10>, Sched<6, 10>, Sched<6, 10>,
                             256, 480, true, true>;
-using R96 = ReducedPipeline<float, 48, 72, 16, 8, 576, Sched<9, 8>, Sched<9, 8>, Sched<9, 8>, 256,
+using R96 = ReducedPipeline<float, 48, 72, 16, 8, 384, Sched<9, 8>, Sched<9, 8>, Sched<9, 8>, 256,
                             512, true, true>;
-using R108 = ReducedPipeline<float, 54, 80, 16, 8, 640, Sched<10, 8>, Sched<10, 8>, Sched<10, 8>,
+using R108 = ReducedPipeline<float, 54, 80, 16, 8, 480, Sched<10, 8>, Sched<10, 8>, Sched<10, 8>,
                              256, 512, true, true>;
 using R120 = ReducedPipeline<float, 60, 96, 16, 8, 768, Sched<12, 8>, Sched<12, 8>, Sched<8, 12>,
                              256, 512, true, true>;
 using R128 = ReducedPipeline<float, 64, 96, 16, 8, 768, Sched<12, 8>, Sched<12, 8>, Sched<8, 12>,
                              256, 512, true, true>;
-using R64x128 = ReducedPipeline<float, 32, 48, 16, 8, 384, Sched<6, 8>, Sched<6, 8>, Sched<8, 12>,
+using R64x128 = ReducedPipeline<float, 32, 48, 16, 8, 256, Sched<6, 8>, Sched<6, 8>, Sched<8, 12>,
                                 256, 512, true, true, 0, 64, 96>;
 }  // namespace
 

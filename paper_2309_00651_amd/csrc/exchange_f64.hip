@@ -7,16 +7,21 @@ namespace {
 // Plane threads: a float64 plane of 64^2 points or more leaves room for one
 // or two workgroups per compute unit, so the plane kernels take 8 threads
 // per row (the alternatives with 4 per row are kept for the autotuner).
-using P24 = FusedPipeline<double, 24, 16, 8, Sched<4, 6>, Sched<6, 4>, 144, Sched<4, 6>,
-                          Sched<6, 4>, Sched<4, 6>, Sched<6, 4>>;
+// The accumulation passes of 24 to 72 and 96 prefetch with the psi J block in
+// LDS (ms per pass, without / with: 64 orbitals on 64^3 1.92 / 1.84, on 72^3
+// 3.16 / 3.06, on 96^3 6.26 / 6.13 with 512 threads; 80^3 is not faster); the
+// smallest grid, bound by its chain of transforms, takes a thread per point (8
+// orbitals on 24^3: 28 -> 22 us).
+using P24 = FusedPipeline<double, 24, 16, 8, Sched<4, 6>, Sched<4, 6>, 144, Sched<4, 6>,
+                          Sched<6, 4>, Sched<4, 6>, Sched<6, 4>, false, 192, 384, true, true>;
 using P64 = FusedPipeline<double, 64, 16, 8, Sched<8, 8>, Sched<8, 8>, 512, Sched<8, 8>,
-                          Sched<8, 8>, Sched<8, 8>, Sched<8, 8>>;
+                          Sched<8, 8>, Sched<8, 8>, Sched<8, 8>, false, 256, 512, true, true>;
 using P72 = FusedPipeline<double, 72, 16, 8, Sched<8, 9>, Sched<9, 8>, 576, Sched<8, 9>,
-                          Sched<9, 8>, Sched<8, 9>, Sched<9, 8>>;
+                          Sched<9, 8>, Sched<8, 9>, Sched<9, 8>, false, 256, 576, true, true>;
 using P80 = FusedPipeline<double, 80, 16, 8, Sched<8, 10>, Sched<10, 8>, 640, Sched<8, 10>,
                           Sched<10, 8>, Sched<8, 10>, Sched<10, 8>>;
 using P96 = FusedPipeline<double, 96, 16, 8, Sched<8, 12>, Sched<12, 8>, 768, Sched<8, 12>,
-                          Sched<12, 8>, Sched<8, 12>, Sched<12, 8>>;
+                          Sched<12, 8>, Sched<8, 12>, Sched<12, 8>, false, 256, 512, true, true>;
 using P64q256 = FusedPipeline<double, 64, 16, 8, Sched<8, 8>, Sched<8, 8>, 256, Sched<8, 8>,
                               Sched<8, 8>, Sched<8, 8>, Sched<8, 8>>;
 using P72q216 = FusedPipeline<double, 72, 16, 8, Sched<8, 9>, Sched<9, 8>, 216, Sched<8, 9>,
@@ -64,22 +69,25 @@ using P128z = SplitPipeline<double, 128, 16, 256, 8, Sched<8, 16>, Sched<16, 8>,
                             Sched<8, 16>, Sched<16, 8>, Sched<8, 16>, Sched<16, 8>>;
 // Reduced pair grids (see exchange_f32.hip).  Every plane of these fits in LDS,
 // also where the caller's grid takes the split plane pass.
-using R64 = ReducedPipeline<double, 32, 48, 16, 8, 384, Sched<6, 8>, Sched<6, 8>, Sched<6, 8>, 256,
-                            384, false, false>;
+// Accumulation with prefetch and the psi J block in LDS (64 orbitals, ms per
+// pass without / with: 64^3 1.264 / 0.848 with 256 threads, 96^3 2.94 / 2.73,
+// 120^3 5.60 / 5.32 with 512 threads).
+using R64 = ReducedPipeline<double, 32, 48, 16, 8, 256, Sched<6, 8>, Sched<6, 8>, Sched<8, 6>, 256,
+                            256, true, true>;
 using R72 = ReducedPipeline<double, 36, 60, 16, 8, 480, Sched<6, 10>, Sched<6, 10>, Sched<6, 10>,
-                            288, 480, false, false>;
+                            256, 480, true, true>;
 using R80 = ReducedPipeline<double, 40, 60, 16, 8, 480, Sched<6, 10>, Sched<6, 10>, Sched<6, 10>,
-                            320, 480, false, false>;
-using R96 = ReducedPipeline<double, 48, 72, 16, 8, 576, Sched<9, 8>, Sched<9, 8>, Sched<9, 8>, 384,
-                            576, false, false>;
+                            256, 480, true, true>;
+using R96 = ReducedPipeline<double, 48, 72, 16, 8, 512, Sched<9, 8>, Sched<9, 8>, Sched<9, 8>, 256,
+                            576, true, true>;
 using R108 = ReducedPipeline<double, 54, 80, 16, 8, 640, Sched<10, 8>, Sched<10, 8>, Sched<10, 8>,
-                             432, 640, false, false>;
+                             256, 512, true, true>;
 using R120 = ReducedPipeline<double, 60, 96, 16, 8, 768, Sched<12, 8>, Sched<12, 8>, Sched<12, 8>,
-                             480, 768, false, false>;
+                             256, 512, true, true>;
 using R128 = ReducedPipeline<double, 64, 96, 16, 8, 768, Sched<12, 8>, Sched<12, 8>, Sched<12, 8>,
-                             512, 768, false, false>;
-using R64x128 = ReducedPipeline<double, 32, 48, 16, 8, 384, Sched<6, 8>, Sched<6, 8>, Sched<12, 8>,
-                                512, 768, false, false, 0, 64, 96>;
+                             256, 512, true, true>;
+using R64x128 = ReducedPipeline<double, 32, 48, 16, 8, 256, Sched<6, 8>, Sched<6, 8>, Sched<12, 8>,
+                                256, 512, true, true, 0, 64, 96>;
 }  // namespace
 
 const Variant* variants_f64(int* count) {

@@ -1325,15 +1325,19 @@ __global__ void __launch_bounds__(NT) k_cols_conv(PassGroup grp) {
 // product pass (fewer, longer wavefronts measured fastest), and for the
 // accumulation pass 512, or 1024 for bricks of more than 1536 points (3
 // points per thread keep the tile's psi and accumulators within 128
-// registers, so that whole workgroups fill the compute unit).  float64: 2
-// brick points per thread, or 4 for bricks too large for 768 threads (more
-// threads per workgroup would cap the registers at 128 and spill).
+// registers, so that whole workgroups fill the compute unit).  float64: 256
+// for the product pass of bricks up to 1536 points too (64 orbitals, ms per
+// pass with 2 points per thread / 256 threads: 64^3 1.14 / 0.95, 72^3 2.21 /
+// 1.73, 80^3 2.99 / 2.25, 96^3 4.57 / 3.77; larger bricks hold too many values
+// per thread: 108^3 3.35 / 3.83), else 2 brick points per thread, or 4 for
+// bricks too large for 768 threads (more threads per workgroup would cap the
+// registers at 128 and spill).
 template <typename T, int N, int W, bool FWD>
 constexpr int pencil_threads() {
   if constexpr (sizeof(T) == 4) {
     return FWD ? 256 : (N * W > 1536 ? 1024 : 512);
   } else {
-    return N * W / 2 > 768 ? (N * W + 3) / 4 : (N * W + 1) / 2;
+    return FWD && N * W <= 1536 ? 256 : N * W / 2 > 768 ? (N * W + 3) / 4 : (N * W + 1) / 2;
   }
 }
 // psi_J block in LDS and next-step prefetch in inv_acc: float32 bricks of up
