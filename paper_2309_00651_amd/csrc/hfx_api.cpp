@@ -1521,6 +1521,11 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
   };
   if (hipGetDevice(&p->device) != hipSuccess)
     return cleanup(fail(HFX_EDEVICE, "no HIP device available"));
+  {
+    const hipError_t e = prepare_inverse_sqrt();
+    if (e != hipSuccess)
+      return cleanup(fail(HFX_EDEVICE, std::string("kernel set-up: ") + hipGetErrorString(e)));
+  }
   for (auto& sp : p->sys) {
     hfx_status s;
     if (sp.pv()->prepare) {

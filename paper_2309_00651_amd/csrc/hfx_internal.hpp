@@ -234,6 +234,7 @@ void launch_gram_self_group(const double* const* a, const int* n, const long lon
                             int count, hipStream_t s);
 
 // Orthonormalisation helpers (ortho.hip)
+hipError_t prepare_inverse_sqrt();
 hipError_t launch_inverse_sqrt(double* s, int n, double* work, int max_iter, hipStream_t st);
 void launch_apply_left(const double* m, const double* src, double* dst, int n, long long nr,
                        double* tmp, hipStream_t st);

@@ -9,7 +9,8 @@
 // Every step is three dense float64 products on the matrix cores.
 // Convergence is decided on the device: the step in which max|Z Y - I| <
 // 1e-10 is the last one applied, and a flag in device memory turns the
-// remaining launches into no-ops, so the host never waits.
+// remaining launches into no-ops, so the host never waits; up to 64 orbitals
+// run in one workgroup and one launch.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -86,15 +87,15 @@ __global__ void __launch_bounds__(256) k_gemm_nn_f64(const double* __restrict__ 
       }
 }
 
-// Newton-Schulz state in device memory: st[0] done flag, st[1] completed
-// steps; err: max |Z Y - I| of the current step as the bits of a
-// non-negative double (ordered like the value, so an integer atomic max
-// applies); scal[0] = c.
+// Newton-Schulz state in device memory: done flag, completed steps; err[k % 2]:
+// max |Z Y - I| of step k as the bits of a non-negative double (ordered like
+// the value, so an integer atomic max applies); c.
 struct NsState {
   int done, steps, pad[2];
-  unsigned long long err;
+  unsigned long long err[2];
   double c;
 };
+constexpr double kNsConverged = 1e-10;  // a step that starts closer than this is the last
 
 // c = max row sum of |S| (a bound on the spectral radius of the symmetric S,
 // tight when S is close to diagonal); Y0 = S / c, Z0 = I.
@@ -124,31 +125,25 @@ __global__ void __launch_bounds__(256) k_ns_init(const double* __restrict__ s, i
     st->c = c;
     st->done = 0;
     st->steps = 0;
-    st->err = 0ull;
+    st->err[0] = st->err[1] = 0ull;
   }
 }
 
 // One n x n x n float64 product C = A B on 32 x 32 tiles (4 wavefronts, one
-// 16 x 16 MFMA block each), skipped once the iteration is done.  EPI: the
-// first product of a step, P = Z Y, is stored as T = (3 I - P) / 2 and
-// max |P - I| goes to st->err.
-template <bool EPI>
-__global__ void __launch_bounds__(256) k_ns_gemm(const double* __restrict__ a,
-                                                 const double* __restrict__ b,
-                                                 double* __restrict__ c, int n,
-                                                 NsState* __restrict__ st) {
-  if (st->done) return;
+// 16 x 16 MFMA block each): acc[i] is C[row][col] at rows row + 4 i.
+__device__ __forceinline__ void ns_product(const double* __restrict__ a,
+                                           const double* __restrict__ b, int n, int tile,
+                                           double __attribute__((ext_vector_type(4))) & acc,
+                                           int& row, int& col) {
   constexpr int T = 32, KB = 16;
   __shared__ double as[T][KB + 1];
   __shared__ double bs[KB][T + 1];
-  __shared__ double red[256];
   const int tiles = (n + T - 1) / T;
-  const int row0 = (blockIdx.x / tiles) * T, col0 = (blockIdx.x % tiles) * T;
+  const int row0 = (tile / tiles) * T, col0 = (tile % tiles) * T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = (wave >> 1) * 16, wc = (wave & 1) * 16;
   const int lr = lane & 15, lk = lane >> 4;
-  typedef double f64x4 __attribute__((ext_vector_type(4)));
-  f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+  acc = {0.0, 0.0, 0.0, 0.0};
   for (int k0 = 0; k0 < n; k0 += KB) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -165,38 +160,147 @@ __global__ void __launch_bounds__(256) k_ns_gemm(const double* __restrict__ a,
                                                  0, 0, 0);
     __syncthreads();
   }
+  row = row0 + wr + lk;
+  col = col0 + wc + lr;
+}
+
+// First product of step k, P = Z Y: T = (3 I - P) / 2, max |P - I| to err[k % 2].
+// A step after one that started within kNsConverged ends the iteration.
+__global__ void __launch_bounds__(256) k_ns_first(const double* __restrict__ z,
+                                                  const double* __restrict__ y,
+                                                  double* __restrict__ t, int n, int k,
+                                                  NsState* __restrict__ st) {
+  if (st->done) return;
+  if (k > 0 && __longlong_as_double((long long)st->err[(k - 1) & 1]) < kNsConverged) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->done = 1;
+    return;
+  }
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  f64x4 acc;
+  int row, col;
+  ns_product(z, y, n, blockIdx.x, acc, row, col);
   double m = 0.0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int r = row0 + wr + lk + 4 * i, cc = col0 + wc + lr;
-    if (r < n && cc < n) {
-      if constexpr (EPI) {
-        const double d = acc[i] - (r == cc ? 1.0 : 0.0);
-        m = fmax(m, fabs(d));
-        c[(long long)r * n + cc] = (r == cc ? 1.0 : 0.0) - 0.5 * d;
-      } else {
-        c[(long long)r * n + cc] = acc[i];
-      }
+    const int r = row + 4 * i;
+    if (r < n && col < n) {
+      const double d = acc[i] - (r == col ? 1.0 : 0.0);
+      m = fmax(m, fabs(d));
+      t[(long long)r * n + col] = (r == col ? 1.0 : 0.0) - 0.5 * d;
     }
   }
-  if constexpr (EPI) {
-    red[tid] = m;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (tid < w) red[tid] = fmax(red[tid], red[tid + w]);
-      __syncthreads();
-    }
-    if (tid == 0) atomicMax(&st->err, (unsigned long long)__double_as_longlong(red[0]));
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) m = fmax(m, __shfl_xor(m, s));
+  if (threadIdx.x % 64 == 0)
+    atomicMax(&st->err[k & 1], (unsigned long long)__double_as_longlong(m));
+}
+
+// The other two products of step k side by side, Y T and T Z.
+__global__ void __launch_bounds__(256) k_ns_step(const double* __restrict__ y,
+                                                 const double* __restrict__ t,
+                                                 const double* __restrict__ z,
+                                                 double* __restrict__ yn, double* __restrict__ zn,
+                                                 int n, int k, NsState* __restrict__ st) {
+  if (st->done) return;
+  const int half = gridDim.x / 2;
+  const bool second = (int)blockIdx.x >= half;
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  f64x4 acc;
+  int row, col;
+  ns_product(second ? t : y, second ? z : t, n, second ? blockIdx.x - half : blockIdx.x, acc, row,
+             col);
+  double* c = second ? zn : yn;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (row + 4 * i < n && col < n) c[(long long)(row + 4 * i) * n + col] = acc[i];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->steps = k + 1;
+    st->err[(k + 1) & 1] = 0ull;  // of the next step
   }
 }
 
-// End of a step: count it; once max |Z Y - I| < 1e-10 the step just applied
-// is the last one.
-__global__ void k_ns_latch(NsState* __restrict__ st) {
-  if (st->done) return;
-  st->steps += 1;
-  if (__longlong_as_double((long long)st->err) < 1e-10) st->done = 1;
-  st->err = 0ull;
+// The whole iteration for n <= 64 in one workgroup, Y, Z and T in LDS: 16
+// wavefronts, one 16 x 16 block each; 64 is what the LDS holds three times
+// (96 would need 223 KB).  Launches bound it before, 160 of them and those
+// after convergence empty: orthonormalising 16 / 64 orbitals on 24^3 took 490 /
+// 499 us, now 25 / 79.  From 65 on two launches per step (were four, one of
+// them a single thread): 128 orbitals 599 -> 337 us, 256 936 -> 604.
+constexpr int kNsSmall = 64;
+__global__ void __launch_bounds__(1024) k_ns_small(double* __restrict__ s, int n, int max_iter) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int L = kNsSmall, LD = L + 1;
+  double* y = reinterpret_cast<double*>(smem_raw);
+  double* z = y + L * LD;
+  double* t = z + L * LD;
+  __shared__ double red[L], red2[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  for (int e = tid; e < L * L; e += 1024) {
+    const int r = e / L, c = e % L;
+    y[r * LD + c] = r < n && c < n ? s[(long long)r * n + c] : 0.0;
+    z[r * LD + c] = r == c && r < n ? 1.0 : 0.0;
+    t[r * LD + c] = 0.0;
+  }
+  __syncthreads();
+  if (tid < L) {
+    double a = 0.0;
+    for (int c = 0; c < n; ++c) a += fabs(y[tid * LD + c]);
+    red[tid] = a;
+  }
+  __syncthreads();
+  double cmax = 0.0;
+  for (int r = 0; r < n; ++r) cmax = fmax(cmax, red[r]);
+  for (int e = tid; e < L * L; e += 1024) y[(e / L) * LD + e % L] /= cmax;
+  __syncthreads();
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  const int nb = (n + 15) / 16;
+  const int br = (wave / 4) * 16, bc = (wave % 4) * 16;  // the wavefront's block
+  const bool mine = wave / 4 < nb && wave % 4 < nb;
+  auto product = [&](const double* a, const double* b) {
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < 16 * nb; k += 4)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(br + lr) * LD + k + lk],
+                                                 b[(k + lk) * LD + bc + lr], acc, 0, 0, 0);
+    return acc;
+  };
+  for (int it = 0; it < max_iter; ++it) {
+    double m = 0.0;
+    if (mine) {
+      const f64x4 p = product(z, y);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = br + lk + 4 * i, c = bc + lr;
+        if (r < n && c < n) {
+          const double d = p[i] - (r == c ? 1.0 : 0.0);
+          m = fmax(m, fabs(d));
+          t[r * LD + c] = (r == c ? 1.0 : 0.0) - 0.5 * d;
+        }
+      }
+    }
+#pragma unroll
+    for (int sh = 32; sh > 0; sh >>= 1) m = fmax(m, __shfl_xor(m, sh));
+    if (lane == 0) red2[wave] = m;
+    __syncthreads();
+    f64x4 yn = {0.0, 0.0, 0.0, 0.0}, zn = yn;
+    if (mine) {
+      yn = product(y, t);
+      zn = product(t, z);
+    }
+    double err = 0.0;
+    for (int w = 0; w < 16; ++w) err = fmax(err, red2[w]);
+    __syncthreads();
+    if (mine)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int at = (br + lk + 4 * i) * LD + bc + lr;
+        y[at] = yn[i];
+        z[at] = zn[i];
+      }
+    __syncthreads();
+    if (err < kNsConverged) break;
+  }
+  const double rc = sqrt(cmax);
+  for (int e = tid; e < n * n; e += 1024) s[e] = z[(e / n) * LD + e % n] / rc;
 }
 
 __global__ void __launch_bounds__(256) k_ns_final(const double* __restrict__ z0,
@@ -225,11 +329,23 @@ static void gemm_nn(const double* a, int lda, const double* b, long long ldb, do
                      ldc, M, N, K, alpha, flag);
 }
 
+constexpr int kNsSmallLds = 3 * kNsSmall * (kNsSmall + 1) * 8;
+
+// Raise the dynamic-LDS limit of the one-workgroup iteration.
+hipError_t prepare_inverse_sqrt() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ns_small),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kNsSmallLds);
+}
+
 // s: n x n overlap in, S^(-1/2) out.  work: >= 5 n^2 doubles + 64 bytes.
 // Step k reads (Y, Z)[k % 2] and writes (Y, Z)[(k + 1) % 2]; the final
 // result is Z[steps % 2], read on the device.
 hipError_t launch_inverse_sqrt(double* s, int n, double* work, int max_iter, hipStream_t st) {
   const long long nn = (long long)n * n;
+  if (n <= kNsSmall) {
+    hipLaunchKernelGGL(k_ns_small, dim3(1), dim3(1024), kNsSmallLds, st, s, n, max_iter);
+    return hipGetLastError();
+  }
   double* y[2] = {work, work + nn};
   double* z[2] = {work + 2 * nn, work + 3 * nn};
   double* t = work + 4 * nn;
@@ -239,10 +355,9 @@ hipError_t launch_inverse_sqrt(double* s, int n, double* work, int max_iter, hip
   const unsigned g = (unsigned)(tiles * tiles);
   for (int it = 0; it < max_iter; ++it) {
     const int cur = it & 1, nxt = cur ^ 1;
-    hipLaunchKernelGGL(k_ns_gemm<true>, dim3(g), dim3(256), 0, st, z[cur], y[cur], t, n, state);
-    hipLaunchKernelGGL(k_ns_gemm<false>, dim3(g), dim3(256), 0, st, y[cur], t, y[nxt], n, state);
-    hipLaunchKernelGGL(k_ns_gemm<false>, dim3(g), dim3(256), 0, st, t, z[cur], z[nxt], n, state);
-    hipLaunchKernelGGL(k_ns_latch, dim3(1), dim3(1), 0, st, state);
+    hipLaunchKernelGGL(k_ns_first, dim3(g), dim3(256), 0, st, z[cur], y[cur], t, n, it, state);
+    hipLaunchKernelGGL(k_ns_step, dim3(2 * g), dim3(256), 0, st, y[cur], t, z[cur], y[nxt], z[nxt],
+                       n, it, state);
   }
   const unsigned eb = (unsigned)((nn + 255) / 256);
   hipLaunchKernelGGL(k_ns_final, dim3(eb), dim3(256), 0, st, z[0], z[1], nn, state, s);
