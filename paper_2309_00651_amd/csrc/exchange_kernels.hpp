@@ -1346,6 +1346,18 @@ template <typename T, int N, int W>
 constexpr bool pencil_prefetch() {
   return sizeof(T) == 4 && N * W <= 1728;
 }
+// Form of the accumulation pass: the pipeline's own for unscreened plans; for
+// screened ones psi_J in registers and no prefetch.  A screened tile leaves
+// whole transforms out, so the step that is loaded ahead is often one that is
+// not evaluated, while its registers and LDS cost workgroups per compute unit
+// (ms per pass, prefetching / this form: 128 orbitals, 11 % of the pairs kept,
+// on 96^3 5.07 / 4.39, 108^3 10.6 / 9.15, float64 72^3 (64) 2.8 / 2.22;
+// prefetching over the evaluated transforms alone spills: 5.62 on 96^3).
+template <bool SCR, bool PJL, bool PF, int FLI>
+struct AccForm {
+  static constexpr bool pjl = !SCR && PJL, pf = !SCR && PF, fl = !SCR && FLI != 0;
+  static constexpr int ng = !SCR && FLI == 4 ? 4 : 2;
+};
 template <int... R>
 constexpr void fill_radices(int* dst, int& n, Sched<R...>) {
   const int r[] = {R...};
@@ -1370,8 +1382,6 @@ struct FusedPipeline {
   // grids of a tile row per transform)
   static_assert(FLI == 0 || FLI == 1 || FLI == 4, "flat-load mode");
   static_assert(FLI == 0 || PF, "flat loads are a form of the prefetching accumulation");
-  static constexpr bool FLB = FLI != 0;
-  static constexpr int NGI = FLI == 4 ? 4 : 2;
   static constexpr size_t lds =
       PM == 2 ? (size_t)((N / 2) * (N + 1) > N * (N / 2 + 1) ? (N / 2) * (N + 1) : N * (N / 2 + 1)) *
                     sizeof(cpx<T>)
@@ -1492,25 +1502,26 @@ struct FusedPipeline {
   // instantiations
   template <bool ACC, bool SCR>
   static void inv_launch(const PassGroup& g, int nb, hipStream_t s) {
+    using A = AccForm<SCR, PJL, PF, FLI>;
     // band-limited plans: float32 takes zero-block loads while at least 3/4
     // of the planes are kept and skipped loads below that; float64 (one
     // workgroup per compute unit, registers tight) always skips (measured at
     // 93 of 96 planes and at 29..57 of 64..120)
     const int kept = kz_planes(NZ, g.a[0].kz_max);
     if (kept == NZ) {
-      hipLaunchKernelGGL((k_inv_acc<T, N, W, NTI, TT, SZI, ACC, PJL, PF, SCR, NZ, 0, FLB, NGI>), dim3(nb),
-                         dim3(NTI), 0, s, g);
+      hipLaunchKernelGGL((k_inv_acc<T, N, W, NTI, TT, SZI, ACC, A::pjl, A::pf, SCR, NZ, 0, A::fl, A::ng>),
+                         dim3(nb), dim3(NTI), 0, s, g);
       return;
     }
     if constexpr (sizeof(T) == 4) {
       if (4 * kept >= 3 * NZ) {
-        hipLaunchKernelGGL((k_inv_acc<T, N, W, NTI, TT, SZI, ACC, PJL, PF, SCR, NZ, 1, FLB, NGI>), dim3(nb),
-                           dim3(NTI), 0, s, g);
+        hipLaunchKernelGGL((k_inv_acc<T, N, W, NTI, TT, SZI, ACC, A::pjl, A::pf, SCR, NZ, 1, A::fl, A::ng>),
+                           dim3(nb), dim3(NTI), 0, s, g);
         return;
       }
     }
-    hipLaunchKernelGGL((k_inv_acc<T, N, W, NTI, TT, SZI, ACC, PJL, PF, SCR, NZ, 2, FLB, NGI>), dim3(nb),
-                       dim3(NTI), 0, s, g);
+    hipLaunchKernelGGL((k_inv_acc<T, N, W, NTI, TT, SZI, ACC, A::pjl, A::pf, SCR, NZ, 2, A::fl, A::ng>),
+                       dim3(nb), dim3(NTI), 0, s, g);
   }
   template <bool ACC>
   static void inv_pass(const PassGroup& g, int nb, hipStream_t s) {
@@ -1604,8 +1615,6 @@ struct ReducedPipeline {
   using SXF = typename HalfZ<NF>::type;   // forward x and y
   using SZF = typename HalfZ<NFZ>::type;  // forward z
   static constexpr int QB = NF / 2;
-  static constexpr bool FLB = FLI != 0;
-  static constexpr int NGI = FLI == 4 ? 4 : 2;
   static constexpr size_t lds = (size_t)NI * (NI + 1) * sizeof(cpx<T>);
   static constexpr auto plane_kernel =
       &k_plane_conv<T, NI, NTQ, SXF, SXI, SXF, SYI, false, false, NIZ, QB, false, true, SXF, true,
@@ -1628,7 +1637,8 @@ struct ReducedPipeline {
   // at most two thirds of the planes are kept: pruned loads are skipped
   template <bool ACC, bool SCR>
   static void inv_launch(const PassGroup& g, int nb, hipStream_t s) {
-    hipLaunchKernelGGL((k_inv_acc<T, NI, W, NTI, TT, SZI, ACC, PJL, PF, SCR, NIZ, 2, FLB, NGI>),
+    using A = AccForm<SCR, PJL, PF, FLI>;
+    hipLaunchKernelGGL((k_inv_acc<T, NI, W, NTI, TT, SZI, ACC, A::pjl, A::pf, SCR, NIZ, 2, A::fl, A::ng>),
                        dim3(nb), dim3(NTI), 0, s, g);
   }
   template <bool ACC>
