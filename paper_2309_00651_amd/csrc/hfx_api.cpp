@@ -83,6 +83,7 @@ struct SystemPlan {
   long long nr = 0;
   double dv = 0.0;
   int rows = 8;  // rows per tile pair (a multiple of the variant's tile)
+  bool rows_given = false;  // by rows= or the tuner
   // band limit: pair densities vanish on kz planes |kz| > kz_max (>= nz / 2:
   // no plane is skipped)
   int kz_max = 1 << 30;
@@ -386,10 +387,28 @@ void schedule_all_pairs(SystemPlan& sp, long long tiles_cap) {
   take_schedule(sp, build_schedule(shape_of(sp), tiles_cap));
 }
 
+// Rows per tile pair of a screened schedule: the plan's where the caller (or
+// the tuner) names them, else the most the kernels take.  Few pairs of a tile
+// are left, so its psi and K psi traffic dominates, and taller tiles share
+// the column side among more of them (ms per K psi, 16 / 32 rows, 128 orbitals
+// with 11 % of the pairs kept: 96^3 9.40 / 8.98, 108^3 16.6 / 13.9, 120^3 18.7 /
+// 16.4, float64 96^3 17.2 / 16.4; 64 on 80^3 2.79 / 2.60).  A launch then often
+// holds a single tile pair: its bricks alone have to give 1.5 workgroups per
+// compute unit (80^3 on; 72^3 with 324 bricks 4.54 / 4.66, 64^3 with 256 1.21 /
+// 1.23), and the tile pair has to fit the slots of the plan's batches.  Sets
+// of one 32-row block gain nothing (24 on 80^3 0.55 / 0.58).
+int screened_rows(const SystemPlan& sp) {
+  const bool fits = sp.pv()->max_rows >= kMaxRows && sp.sys.n_orb > kMaxRows &&
+                    sp.slots_per_batch >= kMaxRows * sp.pv()->tile / 2;
+  return !sp.rows_given && fits && bricks_per_tile(sp.pv()) >= 384 ? kMaxRows : sp.rows;
+}
+
 // Screened schedule: the batches fit the unscreened schedule's slots.
 void schedule_kept_pairs(SystemPlan& sp, const std::vector<unsigned char>& keep,
                          const std::vector<int>& perm) {
-  take_schedule(sp, build_screened_schedule(shape_of(sp), sp.slots_per_batch, keep, perm));
+  ScheduleShape sh = shape_of(sp);
+  sh.rows = screened_rows(sp);
+  take_schedule(sp, build_screened_schedule(sh, sp.slots_per_batch, keep, perm));
 }
 
 // v(G)/N_r on the FFT grid.  zero_dc: store 0 at G = 0 (float32 plans take the
@@ -1429,6 +1448,7 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
       int r = rows_v[i] > 0 ? (int)rows_v[i] : default_rows(sp.sys.n_orb);
       r = std::min(r, sp.var->max_rows);
       sp.rows = std::max(t, r / t * t);
+      sp.rows_given = rows_v[i] > 0;
     }
     sp.kz_max = kz_max_for(ecut, sys[i].L[2]);
     sp.kx_max = kz_max_for(ecut, sys[i].L[0]);
@@ -1901,7 +1921,7 @@ const char* hfx_plan_describe(hfx_plan plan, int system) {
                   std::to_string(v->plane_mode == 0 ? v->nt_plane : v->nt_cols) + "/" +
                   std::to_string(v->nt_acc) + " plane=" +
                   (v->plane_mode == 0 ? "fused" : "split") +
-                  " rows=" + std::to_string(sp.rows) +
+                  " rows=" + std::to_string(sp.d_keep ? screened_rows(sp) : sp.rows) +
                   (sp.kz_max < v->nz / 2 ? " kz_max=" + std::to_string(sp.kz_max)
                                           : std::string()) +
                   (half_z(v, sp.kz_max) ? " z_fwd=half(" + sched(v->zh, v->nzh) + ")"
