@@ -103,15 +103,20 @@ typedef struct hfx_plan_t* hfx_plan;
  * column tile): more rows read psi and update K psi of the column tile once
  * per R pairs instead of once per 8 (default 32 for systems of at least 256
  * orbitals, else 16; clamped to 8 for variants that stage the row orbitals
- * in LDS; screened schedules use the same tile pairs with masks of the kept
- * pairs; results agree to rounding, not bitwise, across R); ecut=<Ha>
+ * in LDS; screened schedules use such tile pairs with masks of the kept
+ * pairs, of 32 rows from 80^3 and 33 orbitals on where rows= is left open and
+ * the batches hold one; results agree to rounding, not bitwise, across R);
+ * ecut=<Ha>
  * declares that every orbital lies in the plane-wave sphere (1/2)|G|^2 <=
  * ecut (true of plane-wave orbitals of that cutoff, and kept by linear
  * combinations such as orthonormalisation): pair densities then vanish on the
  * kz planes with |kz| > 2 floor(sqrt(2 ecut) L_z / 2 pi), which the passes
  * skip, and, in float32 plans, where the band fits in half the grid along z
  * (and along x and y on cubic grids), the first pass transforms only the
- * even z points and rows and the plane pass only the band's columns
+ * even z points and rows and the plane pass only the band's columns; where
+ * it fits half of every axis, plans of either precision that leave the
+ * kernel configuration open run the pairs on a smaller grid, which carries
+ * K psi exactly (hfx_plan_describe reports pair_grid=)
  * (results agree with the full transform to rounding; orbitals outside the
  * sphere give wrong results, which check=1 detects); check=1 (or the
  * environment variable HFX_CHECK_INPUTS=1) makes the energy, K psi, matrix
@@ -307,7 +312,7 @@ hfx_status hfx_screen(hfx_plan plan, const double* psi, double rho_cut, long lon
  * equal psi: in place).  pivots: nullable device int array of sum(n_orb)
  * entries receiving the flat grid index (z n + y) n + x of c_k.  Asynchronous
  * on `stream`; the workspace is used as by the other calls.  Linearly
- * dependent orbitals give NaN.  HFX_EINVAL: null pointers or a call during
+ * dependent orbitals give no usable result (NaN, or rounding noise).  HFX_EINVAL: null pointers or a call during
  * graph capture; HFX_EUNSUPPORTED: more than 3500 orbitals in a system.
  */
 hfx_status hfx_scdm(hfx_plan plan, const double* psi, double* phi, int* pivots, void* ws,
