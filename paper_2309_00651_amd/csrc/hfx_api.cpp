@@ -1207,7 +1207,8 @@ hfx_status enq_scdm(hfx_plan plan, SystemPlan& sp, const double* psi, double* ph
     launch_scdm_pivots(ps, n, sp.nr, scratch, qm, piv, st);
     launch_scdm_gather(ps, n, sp.nr, piv, b, st);
     launch_apply_left(b, ps, ph, n, sp.nr, tmp, st);
-    // every pivot step reads Psi once; the columns B Psi read and write it
+    // counted as one read of Psi per pivot, an upper bound (steps skip the blocks
+    // their bounds rule out); the columns B Psi read and write it
     bk.done(nn * npts * 8.0 * (nn + 2.0), 2.0 * nn * npts * (nn + 1.0) + 2.0 * nn * nn * npts);
   }
   HIP_TRY(hipGetLastError());
