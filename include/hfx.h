@@ -312,7 +312,9 @@ hfx_status hfx_screen(hfx_plan plan, const double* psi, double rho_cut, long lon
  * equal psi: in place).  pivots: nullable device int array of sum(n_orb)
  * entries receiving the flat grid index (z n + y) n + x of c_k.  Asynchronous
  * on `stream`; the workspace is used as by the other calls.  Linearly
- * dependent orbitals give no usable result (NaN, or rounding noise).  HFX_EINVAL: null pointers or a call during
+ * dependent or non-finite orbitals give no usable result (NaN, or rounding
+ * noise; the pivots are grid points all the same, never one that holds a NaN
+ * while others are left).  HFX_EINVAL: null pointers or a call during
  * graph capture; HFX_EUNSUPPORTED: more than 3500 orbitals in a system.
  */
 hfx_status hfx_scdm(hfx_plan plan, const double* psi, double* phi, int* pivots, void* ws,

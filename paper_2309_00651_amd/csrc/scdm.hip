@@ -80,7 +80,10 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// w_r = sum_i psi_i(r)^2 and the blocks' maxima (one workgroup per block)
+// w_r = sum_i psi_i(r)^2 and the blocks' maxima (one workgroup per block).
+// Norms are never NaN (here, and by fmax in the updates), and ties go to the
+// smaller index, so every block maximum names a point of the grid, whatever
+// the orbitals hold.
 __global__ void __launch_bounds__(NTS) k_scdm_norms(const double* __restrict__ psi, int n,
                                                      long long nr, ScdmState st) {
   __shared__ double sv[NTS];
@@ -94,6 +97,9 @@ __global__ void __launch_bounds__(NTS) k_scdm_norms(const double* __restrict__ p
       const double x = psi[(long long)i * nr + r];
       s += x * x;
     }
+    // a point with a NaN is never chosen: its norm would neither win nor lose
+    // a comparison and would hide the other points of its block
+    if (!(s >= 0.0)) s = -1.0;
     st.w[r] = s;
   }
   int at = r < nr ? (int)r : INT_MAX;
@@ -164,7 +170,8 @@ __global__ void __launch_bounds__(NTS) k_scdm_update(const double* __restrict__ 
 // were not brought up to date have bounds below it); its column a =
 // (psi_i(c_k))_i is orthogonalised against q_0..q_(k-1) (rows of qm) twice and
 // normalised into q_k.  A vanishing residual (linearly dependent orbitals)
-// gives NaN, which every later result inherits.  Then the bound of the next
+// or a non-finite column gives a NaN direction; the norms it is applied to
+// become zero, and the later pivots are arbitrary points.  Then the bound of the next
 // step: every wavefront takes the best point among its share of the blocks
 // that are up to date and downdates it with q_k; some point has the largest of
 // these norms, so blocks below it cannot hold the next pivot.
