@@ -29,15 +29,13 @@
 #include <type_traits>
 
 #include "hfx_internal.hpp"
+#include "scdm_bound.hpp"
 
 namespace hfx {
 
 namespace {
 constexpr int NTS = 256;   // threads per workgroup and points per block
 constexpr int NTP = 1024;  // threads of the pick
-// A candidate's norm as the pick sums it may differ from the update's in the
-// last digits: the bound stays below both.
-constexpr double kBelow = 1.0 - 1e-12;
 
 // State of the blocks: w, and per block its largest w, where, and the number
 // of directions already applied; bound[0]: what a block must reach to matter.
@@ -173,8 +171,9 @@ __global__ void __launch_bounds__(NTS) k_scdm_update(const double* __restrict__ 
 // or a non-finite column gives a NaN direction; the norms it is applied to
 // become zero, and the later pivots are arbitrary points.  Then the bound of the next
 // step: every wavefront takes the best point among its share of the blocks
-// that are up to date and downdates it with q_k; some point has the largest of
-// these norms, so blocks below it cannot hold the next pivot.
+// that are up to date and downdates it with q_k; some point has at least the
+// largest of these norms (less what the two sums of a projection may differ
+// by), so blocks below it cannot hold the next pivot.
 __global__ void __launch_bounds__(NTP) k_scdm_pick(const double* __restrict__ psi, int n,
                                                     long long nr, int k, double* __restrict__ qm,
                                                     int* __restrict__ piv, ScdmState st) {
@@ -255,17 +254,22 @@ __global__ void __launch_bounds__(NTP) k_scdm_pick(const double* __restrict__ ps
   const double inv = nrm > 0.0 ? 1.0 / sqrt(nrm) : NAN;
   for (int i = tid; i < n; i += NTP) qm[(long long)k * n + i] = a[i] * inv;
   // the next step's bound
-  double t = 0.0;
+  double t = 0.0, x2 = 0.0;
   if (ci != INT_MAX)
-    for (int i = lane; i < n; i += 64) t += a[i] * inv * psi[(long long)i * nr + ci];
+    for (int i = lane; i < n; i += 64) {
+      const double x = psi[(long long)i * nr + ci];
+      t += a[i] * inv * x;
+      x2 += x * x;
+    }
   t = wave_sum(t);
+  x2 = wave_sum(x2);
   __syncthreads();
-  if (lane == 0) sv[wave] = ci == INT_MAX ? 0.0 : cand - t * t;
+  if (lane == 0) sv[wave] = ci == INT_MAX ? 0.0 : scdm_lower_bound(cand, t, x2, n);
   __syncthreads();
   if (tid == 0) {
     double m = 0.0;
     for (int u = 0; u < WV; ++u) m = sv[u] > m ? sv[u] : m;
-    st.bound[0] = m * kBelow;
+    st.bound[0] = m;
   }
 }
 
