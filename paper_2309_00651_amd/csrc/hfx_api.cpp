@@ -108,6 +108,7 @@ struct SystemPlan {
   // reduced plans: psi at the sampling points (float64; float32 plans also
   // float32 at off_psi32), psi and K psi on the pair grid
   size_t off_samp = 0, off_psig = 0, off_kpsig = 0;
+  size_t off_scale = 0;  // float64 reduced plans: the orbitals' scales of the split products
   size_t off_psi32 = 0, off_grids = 0, off_partials = 0, off_gemm = 0, off_ortho = 0;
   // K psi staging of the gradient (float32 plans) and of hfx_exchange_matrix
   // (both precisions): n_orb x N_r values of the working precision
@@ -411,14 +412,15 @@ void schedule_kept_pairs(SystemPlan& sp, const std::vector<unsigned char>& keep,
   take_schedule(sp, build_screened_schedule(sh, sp.slots_per_batch, keep, perm));
 }
 
-// v(G)/N_r on the FFT grid.  zero_dc: store 0 at G = 0 (float32 plans take the
+// mix v(G) / points on the FFT grid s.n (points: those the forward transforms
+// sum; on reduced grids an eighth of the caller's, so that both paths hold the
+// same values up to a power of two).  zero_dc: store 0 at G = 0 (float32 plans take the
 // G = 0 term out of the transforms, see run_exchange).
 template <typename T>
-std::vector<T> kernel_table(const hfx_system& s, bool zero_dc, double scale) {
+std::vector<T> kernel_table(const hfx_system& s, bool zero_dc, double mix, double points) {
   const double pi = 3.14159265358979323846;
   const double om = s.L[0] * s.L[1] * s.L[2];
   const int nx = s.n[0], ny = s.n[1], nz = s.n[2];
-  const double nr = (double)nx * ny * nz;
   const double rc = std::cbrt(3.0 * om / (4.0 * pi));
   std::vector<T> out((size_t)nx * ny * nz);
   auto freq = [](int k, int n) { return k < (n + 1) / 2 ? k : k - n; };
@@ -441,7 +443,7 @@ std::vector<T> kernel_table(const hfx_system& s, bool zero_dc, double scale) {
           const double w = s.param;
           v = g2 == 0.0 ? pi / (w * w) : -4 * pi * std::expm1(-g2 / (4 * w * w)) / g2;
         }
-        out[((size_t)z * ny + y) * nx + x] = T(scale * v / nr);
+        out[((size_t)z * ny + y) * nx + x] = T(mix * v / points);
       }
   if (zero_dc) out[0] = T(0);
   return out;
@@ -722,8 +724,9 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
         launch_resample(psi, reinterpret_cast<float*>(ws + sp.off_psig), no, n, nz, v->n, v->nz,
                         rx, rz, ws + sp.off_grids, sp.grid_bytes, st);
       else
-        launch_resample(psi, reinterpret_cast<double*>(ws + sp.off_psig), no, n, nz, v->n, v->nz,
-                        rx, rz, ws + sp.off_grids, sp.grid_bytes, st);
+        launch_resample_split(psi, reinterpret_cast<double*>(ws + sp.off_psig), no, n, nz, v->n,
+                              v->nz, rx, rz, reinterpret_cast<double*>(ws + sp.off_scale),
+                              ws + sp.off_grids, sp.grid_bytes, st);
       br.done(orb_pts * 12.0, 0.0);
       psi_w = samp32 ? static_cast<const void*>(samp32) : samp;
     } else if (joint) {
@@ -945,9 +948,10 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
                         static_cast<float*>(calls[c].kpsi), no, v->n, v->nz, n, nz, rx, rz,
                         ws + sp.off_grids, sp.grid_bytes, st);
       else
-        launch_resample(reinterpret_cast<const double*>(ws + sp.off_kpsig),
-                        static_cast<double*>(calls[c].kpsi), no, v->n, v->nz, n, nz, rx, rz,
-                        ws + sp.off_grids, sp.grid_bytes, st);
+        launch_resample_split(reinterpret_cast<const double*>(ws + sp.off_kpsig),
+                              static_cast<double*>(calls[c].kpsi), no, v->n, v->nz, n, nz, rx, rz,
+                              reinterpret_cast<double*>(ws + sp.off_scale), ws + sp.off_grids,
+                              sp.grid_bytes, st);
       bk.done((double)no * ((double)sp.nr + (double)sp.grid_points()) * elem, 0.0);
     }
   for (int c = 0; c < nc; ++c) {
@@ -1474,6 +1478,7 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
         take(&sp.off_samp, no * sp.sample_points() * 8);
         take(&sp.off_psig, no * sp.grid_points() * elem);
         take(&sp.off_kpsig, no * sp.grid_points() * elem);
+        take(&sp.off_scale, precision == HFX_FP64 ? resample_scale_bytes(sys[i].n_orb) : 0);
       }
       take(&sp.off_psi32, precision == HFX_FP32 ? no * sp.sample_points() * 4 : 0);
       sp.nstreams = (sp.batches.size() > 1 && batch_streams == 2) ? 2 : 1;
@@ -1559,18 +1564,16 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
     // the gradient alike
     sp.v0 = mix * kernel_g0(sp.sys);
     const Variant* v = sp.pv();
-    // on reduced grids the forward transforms sum sample_points() values
     hfx_system gs = sp.sys;
-    double vscale = mix;
     if (sp.rvar) {
       gs.n[0] = gs.n[1] = v->n;
       gs.n[2] = v->nz;
-      vscale *= (double)sp.grid_points() / (double)sp.sample_points();
     }
+    const double points = (double)sp.sample_points();
     if (precision == HFX_FP64)
-      s = upload(kernel_table<double>(gs, false, vscale), &sp.vtab);
+      s = upload(kernel_table<double>(gs, false, mix, points), &sp.vtab);
     else
-      s = upload(kernel_table<float>(gs, true, vscale), &sp.vtab);
+      s = upload(kernel_table<float>(gs, true, mix, points), &sp.vtab);
     if (s != HFX_OK) return cleanup(s);
     if (sp.rvar) {
       // bands: orbitals |m| <= kmax / 2, K psi |m| <= 3/2 kmax, for the
@@ -1580,8 +1583,10 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
       const int from[4] = {n, nz, v->n, v->nz}, to[4] = {v->n, v->nz, n, nz};
       const int band[4] = {bx, bz, 3 * bx, 3 * bz};
       for (int k = 0; k < 4; ++k) {
-        std::vector<double> m(resample_entries(from[k], to[k]));
-        resample_matrix(from[k], to[k], band[k], m.data());
+        const bool split = precision == HFX_FP64;
+        std::vector<double> m(split ? resample_split_entries(from[k], to[k])
+                                    : resample_entries(from[k], to[k]));
+        (split ? resample_split_matrix : resample_matrix)(from[k], to[k], band[k], m.data());
         s = upload(m, &sp.d_rs[k]);
         if (s != HFX_OK) return cleanup(s);
       }

@@ -175,11 +175,19 @@ void launch_decimate(const double* psi, int n_orb, int n, int nz, double* out64,
 // the order of the kernels' matrix fragments (host; resample_entries values).
 size_t resample_entries(int a, int b);
 void resample_matrix(int a, int b, int kmax, double* out);
+// The same for float64 plans: folded, high and low parts.
+size_t resample_split_entries(int a, int b);
+void resample_split_matrix(int a, int b, int kmax, double* out);
 // n_orb grids a x a x az -> b x b x bz (float32 sources: b > a) with the
 // matrices rx (x and y) and rz, through tmp (tmp_bytes; at least
 // resample_tmp_bytes for one orbital).
 size_t resample_tmp_bytes(int a, int az, int b, int bz);
 hipError_t prepare_resample();
+// float64 plans, results rounded once per axis; part: resample_scale_bytes.
+size_t resample_scale_bytes(int n_orb);
+void launch_resample_split(const double* in, double* out, int n_orb, int a, int az, int b, int bz,
+                           const double* rx, const double* rz, double* part, void* tmp,
+                           size_t tmp_bytes, hipStream_t s);
 template <typename S, typename O>
 void launch_resample(const S* in, O* out, int n_orb, int a, int az, int b, int bz,
                      const double* rx, const double* rz, void* tmp, size_t tmp_bytes,

@@ -1,0 +1,80 @@
+"""Reduced pair grids in float64 lose nothing against the caller's grid: K psi
+of both against 80-bit arithmetic.  The orbitals are synthesised in 80 bits and
+rounded once, so what they hold outside the declared band is one rounding.  Both
+paths round the same transforms; the reduced one rounds psi and K psi three
+times more each (six times 2^-53 / sqrt(3), 1.6e-16 together, on the caller's
+grid's 2.5e-16), hence the bar of 1.5 times its error."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2309_00651_amd import hfx
+
+pytestmark = pytest.mark.gpu
+
+LD = np.longdouble
+H = 23.5 / 96
+PI = LD("3.14159265358979323846264338327950288")
+
+
+def _orbitals(n, n_orb):
+    """Random plane waves of 5 Ha, 80 bits."""
+    g = 2 * np.pi * np.fft.fftfreq(n, 1 / n) / (n * H)
+    g2 = g[:, None, None] ** 2 + g[None, :, None] ** 2 + g[None, None, : n // 2 + 1] ** 2
+    rng = np.random.default_rng(n)
+    c = rng.standard_normal((n_orb, *g2.shape)) + 1j * rng.standard_normal((n_orb, *g2.shape))
+    c *= np.exp(-g2 / 8) * (0.5 * g2 <= 5.0)
+    psi = np.fft.irfftn(c.astype(np.clongdouble), s=(n, n, n), axes=(1, 2, 3))
+    return psi / np.sqrt((psi ** 2).sum((1, 2, 3), keepdims=True) * H ** 3)
+
+
+def _kpsi(psi, n):
+    g = 2 * PI * np.round(np.fft.fftfreq(n, 1 / n)).astype(LD) / (n * LD(H))
+    g2 = g[:, None, None] ** 2 + g[None, :, None] ** 2 + g[None, None, : n // 2 + 1] ** 2
+    rc = np.cbrt(3 * (n * LD(H)) ** 3 / (4 * PI))
+    safe = np.where(g2 > 0, g2, 1)
+    v = np.where(g2 > 0, 8 * PI * np.sin(rc * np.sqrt(safe) / 2) ** 2 / safe, 2 * PI * rc * rc)
+    out = np.zeros_like(psi)
+    for i in range(len(psi)):
+        for j in range(i, len(psi)):
+            w = np.fft.irfftn(np.fft.rfftn(psi[i] * psi[j], axes=(0, 1, 2)) * v, s=(n, n, n), axes=(0, 1, 2))
+            out[i] -= w * psi[j]
+            if j != i:
+                out[j] -= w * psi[i]
+    return out
+
+
+@pytest.mark.parametrize("n", [64, 80])
+def test_float64_kpsi_is_as_accurate_as_on_the_callers_grid(n):
+    psi = _orbitals(n, 6).astype(np.float64)
+    ref = _kpsi(psi.astype(LD), n)
+    x = torch.from_numpy(psi).cuda()
+    err = []
+    for options in (None, "ecut=5"):
+        plan = hfx.Plan(hfx.SystemSpec(n, (n * H,) * 3, 6), hfx.FP64, options)
+        assert ("pair_grid=" in plan.describe()) == (options is not None)
+        d = plan.apply_exchange(x)[0].cpu().numpy().astype(LD) - ref
+        err.append(float(np.sqrt((d ** 2).sum() / (ref ** 2).sum())))
+    assert err[1] <= 1.5 * err[0], err
+
+
+@pytest.mark.parametrize("n", [64, 108])
+def test_scales_of_the_split_products(n):
+    """A power of two passes through the split products unchanged; an empty and a
+    very small orbital do no harm to the ordinary ones beside them."""
+    n_orb = 9
+    x = torch.from_numpy(_orbitals(n, n_orb).astype(np.float64)).cuda()
+    plan = hfx.Plan(hfx.SystemSpec(n, (n * H,) * 3, n_orb), hfx.FP64, "ecut=5")
+    assert "pair_grid=" in plan.describe()
+    k = plan.apply_exchange(x)[0]
+    for e in (60, -60):
+        assert torch.equal(plan.apply_exchange(x * 2.0 ** e)[0], k * 2.0 ** (3 * e))
+    y = x.clone()
+    y[3] = 0.0
+    y[5] *= 1e-290
+    z = plan.apply_exchange(y)[0]
+    assert torch.isfinite(z).all()
+    rest = [a for a in range(n_orb) if a not in (3, 5)]
+    few = hfx.Plan(hfx.SystemSpec(n, (n * H,) * 3, len(rest)), hfx.FP64)
+    want = few.apply_exchange(x[rest].contiguous())[0]
+    assert float((z[rest] - want).abs().max()) <= 1e-14 * float(want.abs().max())
