@@ -466,8 +466,13 @@ hfx_status upload(const std::vector<T>& h, void** d) {
 }
 
 // float64 tables hold (re, im); float32 tables hold norm-optimised values
-// (unit_f32 in twiddle.hpp).
-hfx_status upload_twiddles(const int* r, int nr_, int prec, void** d) {
+// (unit_f32 in twiddle.hpp), or, on reduced pair grids, balanced ones.  With
+// unit_f32's the reduced grids' float32 results were further off than the
+// caller's grid's: E_x 1.9e-9 / 4.2e-9 (truncated / erfc kernel) against 1.4e-9
+// / 2.8e-9 on 80^3 and 0.8e-9 / 1.8e-9 against 0.6e-9 / 0.9e-9 on 96^3, K psi
+// 6.4e-8 against 6.0e-8 on 108^3 (24 orbitals, against float64).
+hfx_status upload_twiddles(const int* r, int nr_, int prec, bool balanced, void** d) {
+  if (prec != HFX_FP64 && balanced) return upload(balanced_twiddles_f32(r, nr_), d);
   const std::vector<double> t = twiddle_table(r, nr_);
   if (prec == HFX_FP64) return upload(t, d);
   std::vector<float> f(t.size());
@@ -1594,11 +1599,11 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
     const int* rs[6] = {v->zf, v->zi, v->xf, v->xi, v->yf, v->yi};
     const int cs[6] = {v->nzf, v->nzi, v->nxf, v->nxi, v->nyf, v->nyi};
     for (int k = 0; k < 6; ++k) {
-      s = upload_twiddles(rs[k], cs[k], precision, &sp.tw[k]);
+      s = upload_twiddles(rs[k], cs[k], precision, sp.rvar != nullptr, &sp.tw[k]);
       if (s != HFX_OK) return cleanup(s);
     }
     if (v->nzh > 0) {
-      s = upload_twiddles(v->zh, v->nzh, precision, &sp.tw[6]);
+      s = upload_twiddles(v->zh, v->nzh, precision, sp.rvar != nullptr, &sp.tw[6]);
       if (s != HFX_OK) return cleanup(s);
     }
     void* d = nullptr;

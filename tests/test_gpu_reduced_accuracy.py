@@ -1,9 +1,14 @@
-"""Reduced pair grids in float64 lose nothing against the caller's grid: K psi
-of both against 80-bit arithmetic.  The orbitals are synthesised in 80 bits and
+"""Reduced pair grids lose nothing against the caller's grid.
+
+float64: K psi of both against 80-bit arithmetic.  The orbitals are synthesised in 80 bits and
 rounded once, so what they hold outside the declared band is one rounding.  Both
 paths round the same transforms; the reduced one rounds psi and K psi three
 times more each (six times 2^-53 / sqrt(3), 1.6e-16 together, on the caller's
-grid's 2.5e-16), hence the bar of 1.5 times its error."""
+grid's 2.5e-16), hence the bar of 1.5 times its error.
+
+float32: E_x of both against float64, where the error is the transforms' bias:
+no larger on the reduced grid, or below 1e-9 (two codelets in each of six passes,
+each biased by at most 2.5e-10 in amplitude, of either sign)."""
 import numpy as np
 import pytest
 import torch
@@ -78,3 +83,14 @@ def test_scales_of_the_split_products(n):
     few = hfx.Plan(hfx.SystemSpec(n, (n * H,) * 3, len(rest)), hfx.FP64)
     want = few.apply_exchange(x[rest].contiguous())[0]
     assert float((z[rest] - want).abs().max()) <= 1e-14 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("kernel,w", [(hfx.TRUNCATED, 0.0), (hfx.ERFC, 0.106)], ids=["truncated", "erfc"])
+@pytest.mark.parametrize("n", [64, 72, 80, 96, 108, 120, 128])
+def test_float32_energy_is_as_accurate_as_on_the_callers_grid(n, kernel, w):
+    x = torch.from_numpy(_orbitals(n, 9).astype(np.float64)).cuda()
+    spec = hfx.SystemSpec(n, (n * H,) * 3, 9, kernel, w)
+    ref = hfx.Plan(spec, hfx.FP64).exchange_energy(x)
+    err = [abs(float(((hfx.Plan(spec, hfx.FP32, o).exchange_energy(x) - ref) / ref)[0]))
+           for o in (None, "ecut=5")]
+    assert err[1] <= max(err[0], 1e-9), err
