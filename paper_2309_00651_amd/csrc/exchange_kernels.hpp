@@ -129,10 +129,10 @@ __device__ __forceinline__ int next_live_row(unsigned rows, int ia, int nI) {
 // that the loops below issue no global loads besides their own data.
 template <typename T, int TT, int NT, bool SCR>
 __device__ __forceinline__ void stage_means(T* dst, const PassArgs& a, const TileDesc& td,
-                                            double scale, int tid) {
+                                            double scale, int tid, bool own = true) {
   for (int q = tid; q < kMaxRows * TT; q += NT) {
     const int ia = q / TT, b = q - ia * TT;
-    dst[q] = (a.mean && ia < td.nI && b < td.nJ)
+    dst[q] = (a.mean && ia < td.nI && b < td.nJ && (own || td.i0 + ia != td.j0 + b))
                  ? (T)(scale * a.mean[(long long)orb_at<SCR>(a, td.i0 + ia) * a.n_orb +
                                       orb_at<SCR>(a, td.j0 + b)])
                  : T(0);
@@ -447,7 +447,7 @@ __global__ void __launch_bounds__(NT)
   const T* __restrict__ psi = static_cast<const T*>(a.psi);
   T* __restrict__ kpsi = static_cast<T*>(a.kpsi);
   stage_twiddles<T, SZI, NT>(twl, a.tw_zi, tid);
-  stage_means<T, TT, NT, SCR>(dcl, a, td, a.v0, tid);
+  stage_means<T, TT, NT, SCR>(dcl, a, td, a.v0, tid, a.no_own == 0);
   __syncthreads();
   const TwEntry<T>* tw = twl;
   const cpx<T>* __restrict__ grids = static_cast<const cpx<T>*>(a.grids);

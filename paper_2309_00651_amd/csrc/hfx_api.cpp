@@ -659,6 +659,10 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
   // would serialise many small launches); results are those of the
   // per-system launches bit for bit.
   const bool joint = nc > 1 && !reduced;
+  // (a virtual group's share of the pairs may lack the own pairs)
+  auto own_by_resample = [&](const SystemPlan& sp) {
+    return reduced && acc && plan->prec == HFX_FP32 && sp.shards == 1;
+  };
   if (joint) {
     double orbs = 0.0, mean_flops = 0.0;
     for (const SysCall& c : calls) {
@@ -790,6 +794,7 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
     a.kx_max = sp.kx_max;
     a.ky_max = sp.ky_max;
     a.zero = sp.d_zero;
+    a.no_own = own_by_resample(sp) ? 1 : 0;
     max_batches = std::max(max_batches, sp.batches.size());
   }
   const int br = bricks_per_tile(v);
@@ -951,7 +956,10 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       if (plan->prec == HFX_FP32)
         launch_resample(reinterpret_cast<const float*>(ws + sp.off_kpsig),
                         static_cast<float*>(calls[c].kpsi), no, v->n, v->nz, n, nz, rx, rz,
-                        ws + sp.off_grids, sp.grid_bytes, st);
+                        ws + sp.off_grids, sp.grid_bytes, st,
+                        own_by_resample(sp) ? reinterpret_cast<const float*>(ws + sp.off_psig)
+                                            : nullptr,
+                        args[c].mean, sp.v0);
       else
         launch_resample_split(reinterpret_cast<const double*>(ws + sp.off_kpsig),
                               static_cast<double*>(calls[c].kpsi), no, v->n, v->nz, n, nz, rx, rz,

@@ -80,6 +80,9 @@ struct PassArgs {
   // Pass 1: a tile pair's rows are dealt to fwd_chunks workgroups per brick,
   // fwd_rows each (its rows write disjoint pair grids)
   int fwd_rows, fwd_chunks;
+  // Pass 3 leaves out v0 mu_aa psi_a, the own pairs' G = 0 part (added by the
+  // resampling of reduced float32 plans, see launch_resample)
+  int no_own;
 };
 
 // Zero block of band-limited plans (the pruned planes' loads read its first
@@ -178,7 +181,7 @@ void resample_matrix(int a, int b, int kmax, double* out);
 // The same for float64 plans: folded, high and low parts.
 size_t resample_split_entries(int a, int b);
 void resample_split_matrix(int a, int b, int kmax, double* out);
-// n_orb grids a x a x az -> b x b x bz (float32 sources: b > a) with the
+// n_orb grids a x a x az -> b x b x bz (float64 sources: b < a, float32 ones: b > a) with the
 // matrices rx (x and y) and rz, through tmp (tmp_bytes; at least
 // resample_tmp_bytes for one orbital).
 size_t resample_tmp_bytes(int a, int az, int b, int bz);
@@ -191,7 +194,8 @@ void launch_resample_split(const double* in, double* out, int n_orb, int a, int 
 template <typename S, typename O>
 void launch_resample(const S* in, O* out, int n_orb, int a, int az, int b, int bz,
                      const double* rx, const double* rz, void* tmp, size_t tmp_bytes,
-                     hipStream_t s);
+                     hipStream_t s, const S* psi = nullptr, const double* mu = nullptr,
+                     double v0 = 0.0);
 
 // Elementwise helpers (exchange_common.hip)
 void launch_cast_f64_f32(const double* in, float* out, size_t n, hipStream_t s);

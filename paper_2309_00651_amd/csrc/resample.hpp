@@ -160,16 +160,21 @@ void launch_decimate(const double* psi, int n_orb, int n, int nz, double* out64,
 // line at line[q][(lk + j) * stride], fragments as above.  The operands of
 // the next D steps are in flight (a ring of registers): one step's products,
 // RB x NC x 64 cycles, are shorter than an L2 access, and an HBM access
-// takes several.
-template <int RB, int NC, int D, typename S>
+// takes several.  OWN: the line plus own[q] times that at more[q].
+template <int RB, int NC, int D, bool OWN = false, typename S>
 __device__ __forceinline__ void line_products(const S* (&line)[NC], long long stride,
-                                              const double* f, int steps, f64x4 (&acc)[NC][RB]) {
-  S x[D][NC];
+                                              const double* f, int steps, f64x4 (&acc)[NC][RB],
+                                              const S* const* more = nullptr,
+                                              const double* own = nullptr) {
+  S x[D][NC], y[OWN ? D : 1][OWN ? NC : 1];
   double r[D][RB];
   auto load = [&](int k, int s) {
     const int at = s < steps ? s : steps - 1;
 #pragma unroll
-    for (int q = 0; q < NC; ++q) x[k][q] = line[q][at * 4 * stride];
+    for (int q = 0; q < NC; ++q) {
+      x[k][q] = line[q][at * 4 * stride];
+      if constexpr (OWN) y[k][q] = more[q][at * 4 * stride];
+    }
 #pragma unroll
     for (int p = 0; p < RB; ++p) r[k][p] = f[(at * RB + p) * 64];
     asm volatile("" ::: "memory");  // or the loads sink to their use in a later step
@@ -184,12 +189,17 @@ __device__ __forceinline__ void line_products(const S* (&line)[NC], long long st
 #pragma unroll
     for (int k = 0; k < D; ++k) {
       if (s + k < steps) {
+        double v[NC];
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          v[q] = (double)x[k][q];
+          if constexpr (OWN) v[q] += own[q] * (double)y[k][q];
+        }
 #pragma unroll
         for (int p = 0; p < RB; ++p)
 #pragma unroll
           for (int q = 0; q < NC; ++q)
-            acc[q][p] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[k][p], (double)x[k][q], acc[q][p],
-                                                             0, 0, 0);
+            acc[q][p] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[k][p], v[q], acc[q][p], 0, 0, 0);
       }
       load(k, s + k + D);
     }
@@ -200,14 +210,18 @@ __device__ __forceinline__ void line_products(const S* (&line)[NC], long long st
 // an axis that is not the fastest.  A wavefront owns 16 kRsTiles neighbouring columns
 // (of the ng width columns in all), loads their points straight into the B
 // operand (128-byte segments) and keeps all b rows of results: the data moves
-// once, R comes from L2.  a: a multiple of 4.
-template <typename S, typename O, int RB>
+// once, R comes from L2.  a: a multiple of 4.  OWN (K psi back to the caller's
+// grid, group g orbital g): in_g - v0 mu_gg psi_g in place of in_g.
+template <typename S, typename O, int RB, bool OWN>
 __global__ void __launch_bounds__(kRsThreads) k_axis(const S* __restrict__ in, O* __restrict__ out,
                                              const double* __restrict__ frag, int a, int b,
-                                             int width, long long columns) {
+                                             int width, long long columns,
+                                             const S* __restrict__ psi,
+                                             const double* __restrict__ mu, int n_orb, double v0) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lk = lane >> 4;
-  const S* src[kRsTiles];
+  const S *src[kRsTiles], *more[kRsTiles];
+  double own[kRsTiles];
   O* dst[kRsTiles];
   bool ok[kRsTiles];
 #pragma unroll
@@ -217,10 +231,12 @@ __global__ void __launch_bounds__(kRsThreads) k_axis(const S* __restrict__ in, O
     const long long g = ok[q] ? col / width : 0;
     const long long c = ok[q] ? col - g * width : 0;
     src[q] = in + (g * a + lk) * width + c;
+    more[q] = OWN ? psi + (g * a + lk) * width + c : nullptr;
+    own[q] = OWN ? -v0 * mu[g * (n_orb + 1)] : 0.0;
     dst[q] = out + (g * b + lk) * width + c;
   }
   f64x4 acc[kRsTiles][RB];
-  line_products<RB, kRsTiles, 2>(src, width, frag + lane, a / 4, acc);
+  line_products<RB, kRsTiles, 2, OWN>(src, width, frag + lane, a / 4, acc, more, own);
   // result i of lane l: row 16 p + l / 16 + 4 i, column l % 16
 #pragma unroll
   for (int q = 0; q < kRsTiles; ++q)
@@ -498,14 +514,15 @@ static void with_half_rows(int b, F&& f) {
   }
 }
 
-template <typename S, typename O>
+template <bool OWN = false, typename S, typename O>
 static void axis(const S* in, O* out, const double* frag, int a, int b, int width, long long groups,
-                 hipStream_t s) {
+                 hipStream_t s, const S* psi = nullptr, const double* mu = nullptr, int n_orb = 0,
+                 double v0 = 0.0) {
   const long long columns = groups * width, per = (long long)(kRsThreads / 64) * kRsTiles * 16;
   with_rows(b, [&](auto rb) {
-    hipLaunchKernelGGL((k_axis<S, O, decltype(rb)::value>),
+    hipLaunchKernelGGL((k_axis<S, O, decltype(rb)::value, OWN>),
                        dim3((unsigned)((columns + per - 1) / per)), dim3(kRsThreads), 0, s, in, out, frag,
-                       a, b, width, columns);
+                       a, b, width, columns, psi, mu, n_orb, v0);
   });
 }
 
@@ -591,32 +608,39 @@ void launch_resample_split(const double* in, double* out, int n_orb, int a, int 
 
 size_t resample_scale_bytes(int n_orb) { return (size_t)n_orb * kMaxParts * 8; }
 
+// psi, mu, v0 (float32 K psi back): K psi without v0 mu_aa psi_a came in, psi the
+// orbitals on the pair grid.  That term is the largest of a float32 sum whose
+// other terms would each be rounded at its size; added here, in float64, it is
+// not rounded before the result is.
 template <typename S, typename O>
 void launch_resample(const S* in, O* out, int n_orb, int a, int az, int b, int bz,
                      const double* rx, const double* rz, void* tmp, size_t tmp_bytes,
-                     hipStream_t s) {
+                     hipStream_t s, const S* psi, const double* mu, double v0) {
   const size_t one = resample_tmp_bytes(a, az, b, bz);
   const int per = (int)std::max<size_t>(1, std::min<size_t>(n_orb, tmp_bytes / one));
   const long long na = (long long)az * a * a, nb = (long long)bz * b * b;
   double* t = static_cast<double*>(tmp);
   for (int o = 0; o < n_orb; o += per) {
     const int k = std::min(per, n_orb - o);
-    if constexpr (std::is_same_v<S, double>)
-      if (b < a) {
-        plane_axes(in + o * na, t, rx, a, b, (long long)k * az, s);
-        axis(t, out + o * nb, rz, az, bz, b * b, k, s);
-        continue;
-      }
-    axis(in + o * na, t, rz, az, bz, a * a, k, s);
-    plane_axes(t, out + o * nb, rx, a, b, (long long)k * bz, s);
+    if constexpr (std::is_same_v<S, double>) {
+      plane_axes(in + o * na, t, rx, a, b, (long long)k * az, s);
+      axis(t, out + o * nb, rz, az, bz, b * b, k, s);
+    } else {
+      if (psi)
+        axis<true>(in + o * na, t, rz, az, bz, a * a, k, s, psi + o * na,
+                   mu + (size_t)o * (n_orb + 1), n_orb, v0);
+      else
+        axis(in + o * na, t, rz, az, bz, a * a, k, s);
+      plane_axes(t, out + o * nb, rx, a, b, (long long)k * bz, s);
+    }
   }
 }
 
 template void launch_resample<double, float>(const double*, float*, int, int, int, int, int,
                                              const double*, const double*, void*, size_t,
-                                             hipStream_t);
+                                             hipStream_t, const double*, const double*, double);
 template void launch_resample<float, float>(const float*, float*, int, int, int, int, int,
                                             const double*, const double*, void*, size_t,
-                                            hipStream_t);
+                                            hipStream_t, const float*, const double*, double);
 
 }  // namespace hfx

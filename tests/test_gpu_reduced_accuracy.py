@@ -8,7 +8,8 @@ grid's 2.5e-16), hence the bar of 1.5 times its error.
 
 float32: E_x of both against float64, where the error is the transforms' bias:
 no larger on the reduced grid, or below 1e-9 (two codelets in each of six passes,
-each biased by at most 2.5e-10 in amplitude, of either sign)."""
+each biased by at most 2.5e-10 in amplitude, of either sign); and K psi, no
+further off than on the caller's grid."""
 import numpy as np
 import pytest
 import torch
@@ -94,3 +95,22 @@ def test_float32_energy_is_as_accurate_as_on_the_callers_grid(n, kernel, w):
     err = [abs(float(((hfx.Plan(spec, hfx.FP32, o).exchange_energy(x) - ref) / ref)[0]))
            for o in (None, "ecut=5")]
     assert err[1] <= max(err[0], 1e-9), err
+
+
+@pytest.mark.parametrize("rho_cut", [0.0, 0.3])
+@pytest.mark.parametrize("n", [64, 108])
+def test_float32_kpsi_is_as_accurate_as_on_the_callers_grid(n, rho_cut):
+    """Screened too (some own pairs, int psi_a^2 = 1, are then the only ones of their row)."""
+    n_orb = 21
+    x = torch.from_numpy(_orbitals(n, n_orb).astype(np.float64)).cuda()
+    x[4] *= 0.5  # its own pair, 0.25, is screened out
+    spec = hfx.SystemSpec(n, (n * H,) * 3, n_orb)
+    out, kept = [], []
+    for prec, options in ((hfx.FP64, None), (hfx.FP32, None), (hfx.FP32, "ecut=5")):
+        plan = hfx.Plan(spec, prec, options)
+        if rho_cut:
+            kept.append(plan.screen(x, rho_cut))
+        out.append(plan.apply_exchange(x)[0].double())
+    assert len({k[0] for k in kept}) <= 1
+    err = [float((o - out[0]).norm() / out[0].norm()) for o in out[1:]]
+    assert err[1] <= err[0], err
