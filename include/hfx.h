@@ -118,7 +118,10 @@ typedef struct hfx_plan_t* hfx_plan;
  * kernel configuration open run the pairs on a smaller grid, which carries
  * K psi exactly (hfx_plan_describe reports pair_grid=)
  * (results agree with the full transform to rounding; orbitals outside the
- * sphere give wrong results, which check=1 detects); check=1 (or the
+ * sphere give wrong results, which check=1 detects; a share p of their power
+ * outside changes E_x by up to p where planes are skipped, and by up to its
+ * square root where the orbitals are sampled at every other point, i.e. with
+ * z_fwd=half or pair_grid=); check=1 (or the
  * environment variable HFX_CHECK_INPUTS=1) makes the energy, K psi, matrix
  * and gradient calls check psi first and return HFX_EINVAL, launching
  * nothing else, when an orbital holds a non-finite value or, in a plan with
@@ -127,7 +130,8 @@ typedef struct hfx_plan_t* hfx_plan;
  * the half-length z transform, the plane pass's band columns and its
  * half-height input rely on (direct transforms of every orbital line along
  * each axis in float64; the call then waits for its stream; skipped under
- * graph capture); mix=<a>,
+ * graph capture; float64 plans that check run the pairs on the caller's grid,
+ * so that an accepted share changes E_x by no more than itself); mix=<a>,
  * 0 < a <= 1,
  * is a hybrid functional's exact-exchange fraction: the kernel is scaled by a,
  * so E_x, K psi, M, the gradient and the ACE operator are a times the full

@@ -569,9 +569,13 @@ hfx_status check_call(hfx_plan plan, const void* psi, void* ws, size_t ws_bytes)
   return HFX_OK;
 }
 
-// Largest share of an orbital's z power beyond the plan's orbital band that
-// the input check accepts: such content would change E_x by about this
-// relative amount where the band-limited passes skip planes.
+// Largest share of an orbital's power beyond the plan's orbital band along one
+// axis that the input check accepts: such content changes E_x by about this
+// relative amount where the band-limited passes skip planes (float64 plans on
+// the caller's grid, which check=1 keeps).  Passes that sample the orbitals at
+// every other point (float32 plans of a band within half the grid, reduced pair
+// grids) fold its amplitude into the band: there E_x may change by its square
+// root, 1e-6.
 constexpr double kBandTolerance = 1e-12;
 
 // Input check (option check=1): every orbital finite, and, for band-limited
@@ -1517,7 +1521,11 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
       return o;
     };
     size_t end = layout(off);
-    if (const Variant* r = reduced_variant(sp, precision)) {
+    // float64 plans that check their orbitals accept a small share beyond the
+    // band (kBandTolerance), which the caller's grid only truncates
+    const Variant* r =
+        p->check && precision == HFX_FP64 ? nullptr : reduced_variant(sp, precision);
+    if (r) {
       // its orbital copies must not need more workspace than the smaller
       // pair grids free (many orbitals with few, capped tiles per batch)
       sp.rvar = r;
