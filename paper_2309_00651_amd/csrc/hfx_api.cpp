@@ -1526,12 +1526,21 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
     const Variant* r =
         p->check && precision == HFX_FP64 ? nullptr : reduced_variant(sp, precision);
     if (r) {
-      // its orbital copies must not need more workspace than the smaller
-      // pair grids free (many orbitals with few, capped tiles per batch)
+      // its orbital copies must not need more workspace than the smaller pair
+      // grids free.  They can at default options: fewer bricks per tile pair
+      // let a batch hold more of them (float64 120^3: 8 against 5), and from 113
+      // orbitals there a batch has to give some up; the caller's grid is left
+      // to where a single tile pair does not fit.
+      const long long cap = sp.tiles_cap;
       sp.rvar = r;
-      const size_t rend = layout(off);
+      size_t rend = layout(off);
+      for (int t = sp.tiles_per_batch - 1; rend > end && t > 0; --t) {
+        sp.tiles_cap = t;
+        rend = layout(off);
+      }
       if (rend > end) {
         sp.rvar = nullptr;
+        sp.tiles_cap = cap;
         end = layout(off);
       } else {
         end = rend;
