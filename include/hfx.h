@@ -116,12 +116,16 @@ typedef struct hfx_plan_t* hfx_plan;
  * even z points and rows and the plane pass only the band's columns; where
  * it fits half of every axis, plans of either precision that leave the
  * kernel configuration open run the pairs on a smaller grid, which carries
- * K psi exactly (hfx_plan_describe reports pair_grid=)
+ * K psi exactly, from the orbital count on at which that is faster (9 to 44,
+ * by grid and precision); variant=<the grid's default> asks for it at any
+ * count, other variants run on the caller's grid (hfx_plan_describe reports
+ * pair_grid=<samples>-><points>, or pair_grid=<n_x> where the band fits but the
+ * pairs run on the caller's grid)
  * (results agree with the full transform to rounding; orbitals outside the
  * sphere give wrong results, which check=1 detects; a share p of their power
  * outside changes E_x by up to p where planes are skipped, and by up to its
  * square root where the orbitals are sampled at every other point, i.e. with
- * z_fwd=half or pair_grid=); check=1 (or the
+ * z_fwd=half or pair_grid=a->b); check=1 (or the
  * environment variable HFX_CHECK_INPUTS=1) makes the energy, K psi, matrix
  * and gradient calls check psi first and return HFX_EINVAL, launching
  * nothing else, when an orbital holds a non-finite value or, in a plan with

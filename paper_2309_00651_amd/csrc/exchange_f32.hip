@@ -189,12 +189,19 @@ const Variant* variants_f32(int* count) {
   return v;
 }
 
+// Second argument: the fewest orbitals.  Resampling psi and K psi costs four more
+// launches and n_orb times two grids, forming and transforming fewer points gains
+// with n_orb^2 pairs.  Measured (one K psi, us, caller's grid / reduced, below and
+// from the line): 64^3 40 orbitals 760 / 788, 48 915 / 887; 72^3 24 462 / 501, 28
+// 656 / 635; 80^3 16 293 / 335, 18 446 / 439; 96^3 24 880 / 942, 28 1232 / 1227;
+// 108^3 8 276 / 337, 9 448 / 417; 120^3 16 1034 / 1138, 18 1664 / 1471; 128^3 8 443 /
+// 538, 10 720 / 718; 64^2 x 128 20 473 / 484, 22 547 / 531.
 const Variant* reduced_f32(int* count) {
   static const Variant v[] = {
-      R64::describe("f32-n64-r48"),       R72::describe("f32-n72-r60"),
-      R80::describe("f32-n80-r60"),       R96::describe("f32-n96-r72"),
-      R108::describe("f32-n108-r80"),     R120::describe("f32-n120-r96"),
-      R128::describe("f32-n128-r96"),     R64x128::describe("f32-n64x128-r48x96"),
+      R64::describe("f32-n64-r48", 44),   R72::describe("f32-n72-r60", 26),
+      R80::describe("f32-n80-r60", 18),   R96::describe("f32-n96-r72", 28),
+      R108::describe("f32-n108-r80", 9),  R120::describe("f32-n120-r96", 17),
+      R128::describe("f32-n128-r96", 10), R64x128::describe("f32-n64x128-r48x96", 21),
   };
   *count = (int)(sizeof(v) / sizeof(v[0]));
   return v;

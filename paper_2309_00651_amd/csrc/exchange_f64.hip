@@ -117,12 +117,17 @@ const Variant* variants_f64(int* count) {
   return v;
 }
 
+// The fewest orbitals (see exchange_f32.hip; us, caller's grid / reduced): 64^3 16
+// orbitals 259 / 298, 18 397 / 385; 72^3 16 517 / 532, 18 771 / 703; 80^3 12 404 /
+// 431, 14 553 / 535; 96^3 16 1033 / 1043, 18 1545 / 1337; 108^3 8 514 / 669, 9 832 /
+// 798; 120^3 9 1160 / 1175, 10 1209 / 1205; 128^3 8 825 / 902, 9 1295 / 1222; 64^2 x
+// 128 12 331 / 356, 14 450 / 424.
 const Variant* reduced_f64(int* count) {
   static const Variant v[] = {
-      R64::describe("f64-n64-r48"),       R72::describe("f64-n72-r60"),
-      R80::describe("f64-n80-r60"),       R96::describe("f64-n96-r72"),
-      R108::describe("f64-n108-r80"),     R120::describe("f64-n120-r96"),
-      R128::describe("f64-n128-r96"),     R64x128::describe("f64-n64x128-r48x96"),
+      R64::describe("f64-n64-r48", 17),  R72::describe("f64-n72-r60", 17),
+      R80::describe("f64-n80-r60", 13),  R96::describe("f64-n96-r72", 17),
+      R108::describe("f64-n108-r80", 9), R120::describe("f64-n120-r96", 10),
+      R128::describe("f64-n128-r96", 9), R64x128::describe("f64-n64x128-r48x96", 13),
   };
   *count = (int)(sizeof(v) / sizeof(v[0]));
   return v;

@@ -1654,9 +1654,10 @@ struct ReducedPipeline {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(plane_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   }
-  static Variant describe(const char* name) {
+  static Variant describe(const char* name, int min_orb) {
     Variant v{};
     v.name = name;
+    v.min_orb = min_orb;
     v.n = NI;
     v.nz = NIZ;
     v.nf = NF;

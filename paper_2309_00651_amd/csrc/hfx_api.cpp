@@ -84,6 +84,7 @@ struct SystemPlan {
   double dv = 0.0;
   int rows = 8;  // rows per tile pair (a multiple of the variant's tile)
   bool rows_given = false;  // by rows= or the tuner
+  bool named = false;       // kernel configuration named, by variant= or the tuner
   // band limit: pair densities vanish on kz planes |kz| > kz_max (>= nz / 2:
   // no plane is skipped)
   int kz_max = 1 << 30;
@@ -296,7 +297,8 @@ bool parse_count(const std::string& v, long long* out) {
 // along each axis, twice the orbitals') fits half the points of every axis,
 // so every other sample carries it, and K psi, of band 3/2 k_max, fits the
 // reduced pair grid.  Systems whose plan names a kernel configuration other
-// than the grid's default keep that one.
+// than the grid's default keep that one; naming the default asks for the
+// reduced pipeline at any orbital count.
 const Variant* reduced_variant(const SystemPlan& sp, int prec) {
   if (sp.var != find_variant(sp.sys.n[0], sp.sys.n[2], prec)) return nullptr;
   int count = 0;
@@ -1456,6 +1458,7 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
     SystemPlan& sp = p->sys[i];
     sp.sys = sys[i];
     sp.var = find_variant(sys[i].n[0], sys[i].n[2], precision, vnames[i]);
+    sp.named = !vnames[i].empty();
     sp.tuned = tuned[i] != 0;
     sp.n = sys[i].n[0];
     sp.nr = (long long)sp.n * sp.n * sys[i].n[2];
@@ -1525,6 +1528,8 @@ hfx_status hfx_plan_create(hfx_plan* out, const hfx_system* sys, int n_sys, int 
     // band (kBandTolerance), which the caller's grid only truncates
     const Variant* r =
         p->check && precision == HFX_FP64 ? nullptr : reduced_variant(sp, precision);
+    // few orbitals: resampling them costs more than their pairs gain
+    if (r && !sp.named && sys[i].n_orb < r->min_orb) r = nullptr;
     if (r) {
       // its orbital copies must not need more workspace than the smaller pair
       // grids free.  They can at default options: fewer bricks per tile pair
@@ -1966,7 +1971,8 @@ const char* hfx_plan_describe(hfx_plan plan, int system) {
                   (half_x(v, sp.kx_max, sp.ky_max) ? " x_cols=half" : std::string()) +
                   (sp.rvar ? " pair_grid=" + std::to_string(sp.rvar->nf) + "->" +
                                  std::to_string(sp.rvar->n)
-                           : std::string()) +
+                   : reduced_variant(sp, plan->prec) ? " pair_grid=" + std::to_string(sp.n)
+                                                     : std::string()) +
                   " tiles_per_batch=" + std::to_string(sp.tiles_per_batch) +
                   " batches=" + std::to_string(sp.batches.size()) +
                   " streams=" + std::to_string(sp.nstreams) +

@@ -134,6 +134,7 @@ struct Variant {
   int n;           // grid points along x and y
   int nz;          // grid points along z (n for cubic grids)
   int nf, nfz;     // reduced pair grids: sampling points of the forward transforms, else 0
+  int min_orb;     // and the fewest orbitals for which plans that name no variant take them
   int prec;        // 0 float32, 1 float64
   int brick;       // pencil width W (x values per workgroup)
   int tile;        // orbital tile T (columns of a tile pair)

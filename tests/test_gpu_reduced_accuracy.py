@@ -34,6 +34,11 @@ def _orbitals(n, n_orb):
     return psi / np.sqrt((psi ** 2).sum((1, 2, 3), keepdims=True) * H ** 3)
 
 
+def _reduced(n, prec):
+    """Plan options that ask for the reduced grid at any orbital count."""
+    return "ecut=5;variant=" + hfx.variants(n, prec)[0]
+
+
 def _kpsi(psi, n):
     g = 2 * PI * np.round(np.fft.fftfreq(n, 1 / n)).astype(LD) / (n * LD(H))
     g2 = g[:, None, None] ** 2 + g[None, :, None] ** 2 + g[None, None, : n // 2 + 1] ** 2
@@ -56,9 +61,9 @@ def test_float64_kpsi_is_as_accurate_as_on_the_callers_grid(n):
     ref = _kpsi(psi.astype(LD), n)
     x = torch.from_numpy(psi).cuda()
     err = []
-    for options in (None, "ecut=5"):
+    for options in (None, _reduced(n, hfx.FP64)):
         plan = hfx.Plan(hfx.SystemSpec(n, (n * H,) * 3, 6), hfx.FP64, options)
-        assert ("pair_grid=" in plan.describe()) == (options is not None)
+        assert ("->" in plan.describe()) == (options is not None)
         d = plan.apply_exchange(x)[0].cpu().numpy().astype(LD) - ref
         err.append(float(np.sqrt((d ** 2).sum() / (ref ** 2).sum())))
     assert err[1] <= 1.5 * err[0], err
@@ -70,8 +75,8 @@ def test_scales_of_the_split_products(n):
     very small orbital do no harm to the ordinary ones beside them."""
     n_orb = 9
     x = torch.from_numpy(_orbitals(n, n_orb).astype(np.float64)).cuda()
-    plan = hfx.Plan(hfx.SystemSpec(n, (n * H,) * 3, n_orb), hfx.FP64, "ecut=5")
-    assert "pair_grid=" in plan.describe()
+    plan = hfx.Plan(hfx.SystemSpec(n, (n * H,) * 3, n_orb), hfx.FP64, _reduced(n, hfx.FP64))
+    assert "->" in plan.describe()
     k = plan.apply_exchange(x)[0]
     for e in (60, -60):
         assert torch.equal(plan.apply_exchange(x * 2.0 ** e)[0], k * 2.0 ** (3 * e))
@@ -93,7 +98,7 @@ def test_float32_energy_is_as_accurate_as_on_the_callers_grid(n, kernel, w):
     spec = hfx.SystemSpec(n, (n * H,) * 3, 9, kernel, w)
     ref = hfx.Plan(spec, hfx.FP64).exchange_energy(x)
     err = [abs(float(((hfx.Plan(spec, hfx.FP32, o).exchange_energy(x) - ref) / ref)[0]))
-           for o in (None, "ecut=5")]
+           for o in (None, _reduced(n, hfx.FP32))]
     assert err[1] <= max(err[0], 1e-9), err
 
 
@@ -106,7 +111,7 @@ def test_float32_kpsi_is_as_accurate_as_on_the_callers_grid(n, rho_cut):
     x[4] *= 0.5  # its own pair, 0.25, is screened out
     spec = hfx.SystemSpec(n, (n * H,) * 3, n_orb)
     out, kept = [], []
-    for prec, options in ((hfx.FP64, None), (hfx.FP32, None), (hfx.FP32, "ecut=5")):
+    for prec, options in ((hfx.FP64, None), (hfx.FP32, None), (hfx.FP32, _reduced(n, hfx.FP32))):
         plan = hfx.Plan(spec, prec, options)
         if rho_cut:
             kept.append(plan.screen(x, rho_cut))
