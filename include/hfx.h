@@ -153,9 +153,9 @@ typedef struct hfx_plan_t* hfx_plan;
  * matrix and gradient calls run systems with the same compiled configuration,
  * kz band and screening state (up to eight) as one class whose batch steps
  * share one launch per pass, with one staging, pair-mean and zero-fill
- * launch for the class; other classes run on forked streams.  By default only
- * systems whose own pass launches are small (fewer than 512 workgroups) are
- * grouped; group=1 groups every system it can, group=0 none (results are the
+ * launch for the class (on reduced pair grids one per system); other classes
+ * run on forked streams.  By default only systems whose own pass launches are
+ * small (fewer than 512 workgroups) and on the caller's grid are grouped; group=1 groups every system it can, group=0 none (results are the
  * same bit for bit; hfx_plan_describe reports class=<k>/<size>).  Uploads the plan's tables
  * (synchronous).  Errors: HFX_EINVAL for null out/sys, n_sys < 1, n <= 0,
  * L <= 0, n_orb < 1, unknown kernel or precision, erfc w <= 0, an unknown

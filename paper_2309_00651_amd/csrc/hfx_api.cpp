@@ -663,7 +663,8 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
   // A class of several systems stages, takes the pair means of and zeroes
   // all its members in one launch each (per-system launches on one stream
   // would serialise many small launches); results are those of the
-  // per-system launches bit for bit.
+  // per-system launches bit for bit.  Systems on reduced pair grids, which share
+  // launches only when asked to (group=1), stage one by one.
   const bool joint = nc > 1 && !reduced;
   // (a virtual group's share of the pairs may lack the own pairs)
   auto own_by_resample = [&](const SystemPlan& sp) {
@@ -1002,8 +1003,14 @@ long long largest_launch(const SystemPlan& sp) {
 // better as separate launch sequences on forked streams, where different
 // passes of different systems overlap (measured on one MI355X: 16 systems
 // of 8-23 orbitals on 24^3, 0.70 ms shared against 1.26 ms forked; 8 of
-// 32 orbitals on 96^3, 15.7 against 15.2 ms).
+// 32 orbitals on 96^3, 15.7 against 15.2 ms).  So do systems on reduced pair
+// grids: their resampling runs system by system, and forked streams overlap it
+// (float64, shared against forked: 4 of 20 orbitals on 64^3 1.31 / 1.21 ms, on
+// 72^3 2.90 / 2.62; 24 and 23 orbitals 0.81 / 0.74 and 1.73 / 1.59).
 constexpr long long kGroupBelowWorkgroups = 512;
+bool groups_by_default(const SystemPlan& sp) {
+  return !sp.rvar && largest_launch(sp) < kGroupBelowWorkgroups;
+}
 
 // The size classes of a plan's systems for the exchange calls: systems with
 // the same kernel configuration, band and screening state share launches
@@ -1016,13 +1023,11 @@ std::vector<std::vector<int>> size_classes(hfx_plan plan) {
   for (int i = 0; i < (int)plan->sys.size(); ++i) {
     const SystemPlan& sp = plan->sys[i];
     bool placed = false;
-    const bool groupable =
-        plan->group == 1 || (plan->group < 0 && largest_launch(sp) < kGroupBelowWorkgroups);
+    const bool groupable = plan->group == 1 || (plan->group < 0 && groups_by_default(sp));
     if (groupable && sp.nstreams == 1 && !sp.pv()->persistent)
       for (auto& c : out) {
         const SystemPlan& f = plan->sys[c[0]];
-        const bool fg =
-            plan->group == 1 || (plan->group < 0 && largest_launch(f) < kGroupBelowWorkgroups);
+        const bool fg = plan->group == 1 || (plan->group < 0 && groups_by_default(f));
         if ((int)c.size() < kMaxGroup && fg && f.pv() == sp.pv() && f.kz_max == sp.kz_max &&
             (f.d_keep != nullptr) == (sp.d_keep != nullptr) && f.nstreams == 1 &&
             !f.pv()->persistent) {
