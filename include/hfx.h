@@ -125,7 +125,7 @@ typedef struct hfx_plan_t* hfx_plan;
  * sphere give wrong results, which check=1 detects; a share p of their power
  * outside changes E_x by up to p where planes are skipped, and by up to its
  * square root where the orbitals are sampled at every other point, i.e. with
- * z_fwd=half or pair_grid=a->b); check=1 (or the
+ * z_fwd=half); check=1 (or the
  * environment variable HFX_CHECK_INPUTS=1) makes the energy, K psi, matrix
  * and gradient calls check psi first and return HFX_EINVAL, launching
  * nothing else, when an orbital holds a non-finite value or, in a plan with
@@ -339,7 +339,8 @@ hfx_status hfx_schedule_info(hfx_plan plan, int system, long long* info);
 /*
  * One-line description of a system's kernel configuration and schedule:
  * variant name, grid, tile and brick sizes, radix schedules (forward/inverse
- * per axis), threads per workgroup (pair_fwd/plane/inv_acc), rows per tile
+ * per axis), threads per workgroup (pair_fwd/plane/inv_acc) of the kernels that
+ * run (on reduced pair grids theirs, not the named variant's), rows per tile
  * pair, tiles per batch, batches, batch streams and whether the pairs are
  * screened.  The text is
  * owned by the plan and valid until the next call of this function on the

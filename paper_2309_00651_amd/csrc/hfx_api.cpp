@@ -743,7 +743,10 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
         launch_resample_split(psi, reinterpret_cast<double*>(ws + sp.off_psig), no, n, nz, v->n,
                               v->nz, rx, rz, reinterpret_cast<double*>(ws + sp.off_scale),
                               ws + sp.off_grids, sp.grid_bytes, st);
-      br.done(orb_pts * 12.0, 0.0);
+      // psi read; its samples (float32 too in float32 plans) and pair grid written
+      br.done((double)no * ((double)sp.nr * 8.0 + (double)sp.sample_points() * (samp32 ? 12.0 : 8.0) +
+                            (double)sp.grid_points() * elem),
+              0.0);
       psi_w = samp32 ? static_cast<const void*>(samp32) : samp;
     } else if (joint) {
       psi_w = plan->prec == HFX_FP32 ? static_cast<const void*>(ws + sp.off_psi32) : psi;
@@ -771,14 +774,15 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
       launch_xtx_f64(ps, ps, sp.sys.n_orb, np, 1.0 / (double)np, part, mu, st);
       // screened pairs contribute no G = 0 energy either
       if (sp.d_keep) launch_mask(mu, sp.d_keep, (size_t)sp.sys.n_orb * sp.sys.n_orb, st);
-      br.done(orb_pts * 8.0, 2.0 * (double)sp.sys.n_orb * orb_pts);
+      const double pts = (double)sp.sys.n_orb * (double)np;
+      br.done(pts * 8.0, 2.0 * (double)sp.sys.n_orb * pts);
       mean = mu;
     }
     if (acc && !joint) {
       Bracket br(plan, HFX_PASS_ZERO, st);
       launch_zero(reduced ? static_cast<void*>(ws + sp.off_kpsig) : calls[c].kpsi,
                   (size_t)sp.sys.n_orb * sp.grid_points() * elem, st);
-      br.done(orb_pts * elem, 0.0);
+      br.done((double)sp.sys.n_orb * (double)sp.grid_points() * elem, 0.0);
     }
     PassArgs& a = args[c];
     a = PassArgs{};
@@ -972,7 +976,9 @@ hfx_status run_exchange(hfx_plan plan, const std::vector<SysCall>& calls, char* 
                               static_cast<double*>(calls[c].kpsi), no, v->n, v->nz, n, nz, rx, rz,
                               reinterpret_cast<double*>(ws + sp.off_scale), ws + sp.off_grids,
                               sp.grid_bytes, st);
-      bk.done((double)no * ((double)sp.nr + (double)sp.grid_points()) * elem, 0.0);
+      bk.done((double)no * ((double)sp.nr + (own_by_resample(sp) ? 2.0 : 1.0) *
+                                                (double)sp.grid_points()) * elem,
+              0.0);
     }
   for (int c = 0; c < nc; ++c) {
     if (!calls[c].ex) continue;
@@ -1951,14 +1957,22 @@ const char* hfx_plan_describe(hfx_plan plan, int system) {
     return nullptr;
   }
   const SystemPlan& sp = plan->sys[system];
-  const Variant* v = sp.var;
+  // the kernels that run: the reduced pipeline's schedules (forward lengths those
+  // of the samples), threads and tiles where there is one
+  const Variant* v = sp.pv();
   auto sched = [](const int* r, int c) {
     std::string o;
     for (int i = 0; i < c; ++i) o += (i ? "x" : "") + std::to_string(r[i]);
     return o;
   };
-  std::string d = std::string("variant=") + v->name + " n=" + std::to_string(v->n) +
-                  (v->nz != v->n ? " nz=" + std::to_string(v->nz) : std::string()) +
+  // pass 1 on every other point (reduced pair grids: along all three axes)
+  const std::string half =
+      sp.rvar ? " z_fwd=half(" + sched(v->zf, v->nzf) + ") y_rows=half x_cols=half"
+              : (half_z(v, sp.kz_max) ? " z_fwd=half(" + sched(v->zh, v->nzh) + ")" : std::string()) +
+                    (half_y(v, sp.kx_max, sp.ky_max) ? " y_rows=half" : "") +
+                    (half_x(v, sp.kx_max, sp.ky_max) ? " x_cols=half" : "");
+  std::string d = std::string("variant=") + sp.var->name + " n=" + std::to_string(sp.n) +
+                  (sp.sys.n[2] != sp.n ? " nz=" + std::to_string(sp.sys.n[2]) : std::string()) +
                   " tile=" + std::to_string(v->tile) + " brick=" + std::to_string(v->brick) +
                   " z=" + sched(v->zf, v->nzf) + "/" + sched(v->zi, v->nzi) +
                   " x=" + sched(v->xf, v->nxf) + "/" + sched(v->xi, v->nxi) +
@@ -1968,12 +1982,9 @@ const char* hfx_plan_describe(hfx_plan plan, int system) {
                   std::to_string(v->nt_acc) + " plane=" +
                   (v->plane_mode == 0 ? "fused" : "split") +
                   " rows=" + std::to_string(sp.d_keep ? screened_rows(sp) : sp.rows) +
-                  (sp.kz_max < v->nz / 2 ? " kz_max=" + std::to_string(sp.kz_max)
-                                          : std::string()) +
-                  (half_z(v, sp.kz_max) ? " z_fwd=half(" + sched(v->zh, v->nzh) + ")"
-                                        : std::string()) +
-                  (half_y(v, sp.kx_max, sp.ky_max) ? " y_rows=half" : std::string()) +
-                  (half_x(v, sp.kx_max, sp.ky_max) ? " x_cols=half" : std::string()) +
+                  (sp.kz_max < sp.sys.n[2] / 2 ? " kz_max=" + std::to_string(sp.kz_max)
+                                               : std::string()) +
+                  half +
                   (sp.rvar ? " pair_grid=" + std::to_string(sp.rvar->nf) + "->" +
                                  std::to_string(sp.rvar->n)
                    : reduced_variant(sp, plan->prec) ? " pair_grid=" + std::to_string(sp.n)
