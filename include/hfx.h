@@ -104,8 +104,8 @@ typedef struct hfx_plan_t* hfx_plan;
  * per R pairs instead of once per 8 (default 32 for systems of at least 256
  * orbitals, else 16; clamped to 8 for variants that stage the row orbitals
  * in LDS; screened schedules use such tile pairs with masks of the kept
- * pairs, of 32 rows from 80^3 and 33 orbitals on where rows= is left open and
- * the batches hold one; results agree to rounding, not bitwise, across R);
+ * pairs, of 32 rows where rows= is left open, the batches hold one and they
+ * are enough fewer; results agree to rounding, not bitwise, across R);
  * ecut=<Ha>
  * declares that every orbital lies in the plane-wave sphere (1/2)|G|^2 <=
  * ecut (true of plane-wave orbitals of that cutoff, and kept by linear

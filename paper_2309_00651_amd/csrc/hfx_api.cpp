@@ -83,6 +83,7 @@ struct SystemPlan {
   long long nr = 0;
   double dv = 0.0;
   int rows = 8;  // rows per tile pair (a multiple of the variant's tile)
+  int tile_rows = 8;  // those of the current schedule (screened ones may take more)
   bool rows_given = false;  // by rows= or the tuner
   bool named = false;       // kernel configuration named, by variant= or the tuner
   // band limit: pair densities vanish on kz planes |kz| > kz_max (>= nz / 2:
@@ -376,7 +377,8 @@ ScheduleShape shape_of(const SystemPlan& sp) {
   return sh;
 }
 
-void take_schedule(SystemPlan& sp, Schedule&& s) {
+void take_schedule(SystemPlan& sp, Schedule&& s, int rows) {
+  sp.tile_rows = rows;
   sp.tiles_per_batch = s.tiles_per_batch;
   sp.slots_per_batch = s.slots_per_batch;
   sp.tiles = std::move(s.tiles);
@@ -387,31 +389,41 @@ void take_schedule(SystemPlan& sp, Schedule&& s) {
 
 // Unscreened schedule of a system (see schedule.hpp).
 void schedule_all_pairs(SystemPlan& sp, long long tiles_cap) {
-  take_schedule(sp, build_schedule(shape_of(sp), tiles_cap));
+  take_schedule(sp, build_schedule(shape_of(sp), tiles_cap), sp.rows);
 }
 
-// Rows per tile pair of a screened schedule: the plan's where the caller (or
-// the tuner) names them, else the most the kernels take.  Few pairs of a tile
-// are left, so its psi and K psi traffic dominates, and taller tiles share
-// the column side among more of them (ms per K psi, 16 / 32 rows, 128 orbitals
-// with 11 % of the pairs kept: 96^3 9.40 / 8.98, 108^3 16.6 / 13.9, 120^3 18.7 /
-// 16.4, float64 96^3 17.2 / 16.4; 64 on 80^3 2.79 / 2.60).  A launch then often
-// holds a single tile pair: its bricks alone have to give 1.5 workgroups per
-// compute unit (80^3 on; 72^3 with 324 bricks 4.54 / 4.66, 64^3 with 256 1.21 /
-// 1.23), and the tile pair has to fit the slots of the plan's batches.  Sets
-// of one 32-row block gain nothing (24 on 80^3 0.55 / 0.58).
-int screened_rows(const SystemPlan& sp) {
-  const bool fits = sp.pv()->max_rows >= kMaxRows && sp.sys.n_orb > kMaxRows &&
-                    sp.slots_per_batch >= kMaxRows * sp.pv()->tile / 2;
-  return !sp.rows_given && fits && bricks_per_tile(sp.pv()) >= 384 ? kMaxRows : sp.rows;
+// Whether a screened schedule takes 32 rows per tile pair where the plan leaves
+// them open: low is the schedule of the plan's rows (16), tall that of 32.  Few
+// pairs of a tile are left, so its psi and K psi traffic dominates, and tall tile
+// pairs share their column side among more rows; but a launch then often holds
+// a single one, whose workgroups each run a longer chain.  What decides is by how
+// much the tile pairs become fewer, less so where one has more bricks (one K
+// psi, 16 over 32 rows, and low over tall tile pairs in brackets, from 3 to 25 % of the
+// pairs kept: 64^3 0.86 [1.06] .. 0.98 [1.43], 1.08 [1.62], 1.12 in float64; 72^3 0.95
+// [1.33], 0.98 [1.50], 1.03 [1.55], 1.13 [1.59]; 80^3 0.89 [1.00], 0.92 [1.09], 0.99
+// [1.33 and 1.39], 1.03 [1.50], 1.10 [1.66]; 96^3 0.98 [1.14], 1.05 [1.17], 1.12 [1.58]; 108^3 and
+// 120^3 1.09 to 1.20 [1.14 to 1.63]; 40 to 200 orbitals, float64 alike).
+bool tall_tiles_pay(const Schedule& low, const Schedule& tall, int bricks) {
+  const double need = bricks >= 729 ? 0.0 : bricks >= 576 ? 1.15 : bricks >= 400 ? 1.3 : 1.52;
+  return (double)low.tiles.size() >= need * (double)tall.tiles.size();
 }
 
 // Screened schedule: the batches fit the unscreened schedule's slots.
 void schedule_kept_pairs(SystemPlan& sp, const std::vector<unsigned char>& keep,
                          const std::vector<int>& perm) {
   ScheduleShape sh = shape_of(sp);
-  sh.rows = screened_rows(sp);
-  take_schedule(sp, build_screened_schedule(sh, sp.slots_per_batch, keep, perm));
+  Schedule low = build_screened_schedule(sh, sp.slots_per_batch, keep, perm);
+  // (sets of one 32-row block gain nothing: 24 orbitals on 80^3 0.55 / 0.58 ms)
+  if (!sp.rows_given && sp.rows < kMaxRows && sp.pv()->max_rows >= kMaxRows &&
+      sp.sys.n_orb > kMaxRows && sp.slots_per_batch >= kMaxRows * sp.pv()->tile / 2) {
+    sh.rows = kMaxRows;
+    Schedule tall = build_screened_schedule(sh, sp.slots_per_batch, keep, perm);
+    if (tall_tiles_pay(low, tall, sh.bricks)) {
+      take_schedule(sp, std::move(tall), kMaxRows);
+      return;
+    }
+  }
+  take_schedule(sp, std::move(low), sp.rows);
 }
 
 // mix v(G) / points on the FFT grid s.n (points: those the forward transforms
@@ -1941,6 +1953,7 @@ hfx_status hfx_screen(hfx_plan plan, const double* psi, double rho_cut, long lon
     sp.active = std::move(ns.active);
     sp.batches = std::move(ns.batches);
     sp.n_partials = ns.n_partials;
+    sp.tile_rows = ns.tile_rows;
     sp.tiles_per_batch = ns.tiles_per_batch;
     sp.slots_per_batch = ns.slots_per_batch;
     sp.d_tiles = static_cast<TileDesc*>(dt);
@@ -1981,7 +1994,7 @@ const char* hfx_plan_describe(hfx_plan plan, int system) {
                   std::to_string(v->plane_mode == 0 ? v->nt_plane : v->nt_cols) + "/" +
                   std::to_string(v->nt_acc) + " plane=" +
                   (v->plane_mode == 0 ? "fused" : "split") +
-                  " rows=" + std::to_string(sp.d_keep ? screened_rows(sp) : sp.rows) +
+                  " rows=" + std::to_string(sp.tile_rows) +
                   (sp.kz_max < sp.sys.n[2] / 2 ? " kz_max=" + std::to_string(sp.kz_max)
                                                : std::string()) +
                   half +
