@@ -50,9 +50,10 @@ struct ResampleKernel {
   std::vector<char> known;
   ResampleKernel(int a_, int b_, int k) : a(a_), b(b_), kmax(k), val(a_ * b_, 0.0L), known(a_ * b_, 0) {}
   // R depends on d = (i/b - j/a) ab mod ab alone; the sum over k in closed form,
-  // sin((2 kmax + 1) pi d / ab) / sin(pi d / ab), its angles reduced exactly
+  // sin((2 kmax + 1) pi d / ab) / sin(pi d / ab), its angles reduced exactly and, as
+  // it is even in d, to the smaller of d and ab - d (no cancellation at the poles)
   long double value(int i, int j) {
-    const int ab = a * b, d = ((i * a - j * b) % ab + ab) % ab;
+    const int ab = a * b, e = ((i * a - j * b) % ab + ab) % ab, d = e < ab - e ? e : ab - e;
     if (!known[d]) {
       const long double pi = 3.14159265358979323846264338327950288L;
       const long long m = (2LL * kmax + 1) * d % (2LL * ab);
